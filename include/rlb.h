@@ -253,14 +253,16 @@ int rlb_set_walls(rlb_solver *s, const uint8_t *solid, void *d_buf, size_t bytes
  * The Riemann problems of Sec. III are one-dimensional: a tube is a periodic
  * 1 x 1 x n lattice on which only the z displacement of each point moves
  * anything.  A batch holds many tubes of one precision in one caller-owned
- * buffer and advances all of them in one persistent launch: one workgroup
- * per tube, launched longest-work-first, whose wavefronts take the tube's
- * (step, chunk) work in order and wait only for the neighbouring chunks'
- * previous step (float64 tubes above 786,432 cells: a workgroup barrier
- * between steps instead).  Every such wait is bounded: after about 0.1 s it
- * gives up and raises RLB_FLAG_STALL in its tube (never expected; the
- * environment variable RLB_TUBE_SPIN_LIMIT, read by rlb_batch_step, lowers
- * the bound to that many polls, for tests of that path).  Tubes never
+ * buffer and advances all of them together.  Many tubes take one persistent
+ * launch: one workgroup per tube, launched longest-work-first, whose
+ * wavefronts take the tube's (step, chunk) work in order and wait only for
+ * the neighbouring chunks' previous step.  Every such wait is bounded: after
+ * about 0.1 s it gives up and raises RLB_FLAG_STALL in its tube (never
+ * expected; the environment variable RLB_TUBE_SPIN_LIMIT, read by
+ * rlb_batch_step, lowers the bound to that many polls, for tests of that
+ * path, and selects this kernel).  Few tubes, or a float64 tube above 786,432
+ * cells, are spread over the chip instead, by launches of up to five steps.
+ * The choice is made at creation from the tubes' lengths.  Tubes never
  * interact; a failure (status flag) stays in its tube. */
 typedef struct rlb_tube {
   int32_t n;        /* cells along z, 1 .. 4,194,304 (2^22)                */
@@ -286,8 +288,8 @@ int rlb_batch_create(rlb_batch **out, const rlb_tube *tubes, int32_t ntubes, int
 int rlb_batch_init(rlb_batch *b, int32_t tube, const double *n, const double *eps, const double *vx,
                    const double *vy, const double *vz, int32_t on_device);
 
-/* One persistent launch: tube j advances steps[j] >= 0 steps (0 leaves it
- * untouched).  Every tube with steps[j] > 0 must have been initialised.
+/* Tube j advances steps[j] >= 0 steps (0 leaves it untouched), all tubes
+ * together.  Every tube with steps[j] > 0 must have been initialised.
  * Asynchronous on the batch's stream. */
 int rlb_batch_step(rlb_batch *b, const int64_t *steps);
 

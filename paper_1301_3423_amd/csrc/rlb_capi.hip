@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "rlb_kernels.hpp"
+#include "rlb_split.hpp"
 
 static_assert(rlb::FLAG_NONFINITE == RLB_FLAG_NONFINITE && rlb::FLAG_NONPHYSICAL == RLB_FLAG_NONPHYSICAL &&
                   rlb::FLAG_LANDAU == RLB_FLAG_LANDAU && rlb::FLAG_TUBE_SYNC == RLB_FLAG_STALL,
@@ -779,6 +780,8 @@ struct rlb_batch {
   int *h_order;
   hipEvent_t staged;
   bool staged_pending;
+  bool flow_fits; // k_tubes has flags for every tube's chunks
+  bool tiles;     // stepped by k_tubes_tile rather than k_tubes
 };
 
 namespace {
@@ -828,6 +831,128 @@ int wait_staged(rlb_batch *b) {
   if (b->staged_pending) {
     RLB_HIP(hipEventSynchronize(b->staged));
     b->staged_pending = false;
+  }
+  return RLB_OK;
+}
+
+// What a step of a batch takes, in us, by kernel: one persistent workgroup
+// per tube (k_tubes) or launches of k steps over 64-lane tiles
+// (k_tubes_tile), from measurements of 1 to 512 tubes of 1 to 4000 cells.
+struct TubeCost {
+  double flow, flow_cell; // the longest tube: flow + flow_cell * cells
+  double flow_rate;       // cells per us with every CU at work
+  double start, step;     // a launch of k steps: start + k * step, or, with
+  double load, work;      // tiles to spare, tiles / 256 * (load + k * work)
+};
+TubeCost tube_cost(int precision, int order) {
+  if (order == RLB_ORDER2)
+    return precision == RLB_FP64 ? TubeCost{3.5, 1.0 / 43, 5000, 3.0, 3.0, 3.4, 1.65}
+                                 : TubeCost{4.0, 1.0 / 90, 10000, 2.5, 2.9, 2.2, 1.75};
+  return precision == RLB_FP64 ? TubeCost{7.0, 1.0 / 21, 2520, 3.5, 4.4, 6.5, 3.6}
+                               : TubeCost{7.0, 1.0 / 45, 5050, 2.9, 4.1, 3.0, 2.6};
+}
+
+int64_t tube_tiles(int32_t n, int k) { return (n + rlb::tube_tile_cells(k) - 1) / rlb::tube_tile_cells(k); }
+
+// Time of `launches` launches of k steps that take `tiles` tiles in all.
+double tile_time(const TubeCost &c, int k, double launches, double tiles) {
+  return launches * c.start + std::max(launches * k * c.step, tiles / 256 * (c.load + k * c.work));
+}
+
+// Whether the tubes are stepped by tiles: from their lengths alone, so that
+// every step of a batch takes the same kernel.  Few tubes, or tubes of very
+// uneven length, leave most CUs without a workgroup of k_tubes; with some
+// 300 tubes or more the persistent kernel, which splits no cell and computes
+// none twice, is the faster (512 tubes of 200-4000 cells: 433 against 526 us
+// per step in float64, 216 against 278 in mixed precision).
+bool tubes_by_tiles(const std::vector<rlb_tube> &tubes, int precision, int order) {
+  const TubeCost c = tube_cost(precision, order);
+  double cells = 0.0;
+  int32_t longest = 0;
+  for (const rlb_tube &t : tubes) {
+    cells += t.n;
+    longest = std::max(longest, t.n);
+  }
+  const double flow = std::max(c.flow + c.flow_cell * longest, cells / c.flow_rate);
+  for (int k = 1; k <= rlb::TUBE_MAX_KSTEPS; ++k) {
+    double tiles = 0.0;
+    for (const rlb_tube &t : tubes) tiles += static_cast<double>(tube_tiles(t.n, k));
+    if (tile_time(c, k, 1.0, tiles) < flow * k) return true;
+  }
+  return false;
+}
+
+// Steps per launch for this call: the k of least estimated time.
+int tile_steps(const rlb_batch *b, const int64_t *steps) {
+  const TubeCost c = tube_cost(b->precision, b->order);
+  int best = 1;
+  double best_time = 0.0;
+  for (int k = 1; k <= rlb::TUBE_MAX_KSTEPS; ++k) {
+    double launches = 0.0, tiles = 0.0;
+    for (int j = 0; j < b->ntubes; ++j) {
+      const double l = static_cast<double>((steps[j] + k - 1) / k);
+      launches = std::max(launches, l);
+      tiles += l * static_cast<double>(tube_tiles(b->tubes[j].n, k));
+    }
+    const double t = tile_time(c, k, launches, tiles);
+    if (k == 1 || t < best_time) {
+      best = k;
+      best_time = t;
+    }
+  }
+  return best;
+}
+
+// Advances the tubes by launches of k_tubes_tile, the tubes with the most
+// steps first, so that those which have finished drop off the grid's end.
+int batch_step_tiles(rlb_batch *b, const int64_t *steps) {
+  const int ksteps = tile_steps(b, steps);
+  std::vector<int> tubes;
+  for (int j = 0; j < b->ntubes; ++j)
+    if (steps[j] > 0) tubes.push_back(j);
+  std::stable_sort(tubes.begin(), tubes.end(), [&](int x, int y) { return steps[x] > steps[y]; });
+  int rc = wait_staged(b);
+  if (rc != RLB_OK) return rc;
+  const int nt = static_cast<int>(tubes.size());
+  std::vector<int> tiles_up_to(nt);
+  int tiles = 0;
+  for (int k = 0; k < nt; ++k) {
+    const int j = tubes[k];
+    b->h_desc[k] = b->desc[j];
+    b->h_desc[k].steps = steps[j];
+    b->h_desc[k].spin_limit = tiles;
+    b->h_order[k] = j;
+    tiles += static_cast<int>(tube_tiles(b->tubes[j].n, ksteps));
+    tiles_up_to[k] = tiles;
+  }
+  RLB_HIP(hipMemcpyAsync(b->d_desc, b->h_desc, nt * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, b->stream));
+  RLB_HIP(hipMemcpyAsync(b->d_order, b->h_order, nt * sizeof(int), hipMemcpyHostToDevice, b->stream));
+  RLB_HIP(hipEventRecord(b->staged, b->stream));
+  b->staged_pending = true;
+  int live = nt;
+  for (int round = 0; live > 0; ++round) {
+    while (live > 0 && steps[tubes[live - 1]] <= static_cast<int64_t>(round) * ksteps) --live;
+    if (live == 0) break;
+    with_model(b->order, [&](auto m) {
+      using M = decltype(m);
+      const auto launch = [&](auto zero) {
+        using S = decltype(zero);
+        constexpr int NG = rlb::Split<M, S>::NG;
+        rlb::k_tubes_tile<M, S><<<dim3(tiles_up_to[live - 1]), dim3(64 * NG), 0, b->stream>>>(
+            reinterpret_cast<S *>(b->pops), b->d_desc, b->d_order, live, round, ksteps, b->d_status);
+      };
+      if (b->precision == RLB_FP64)
+        launch(0.0);
+      else
+        launch(0.0f);
+      return 0;
+    });
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "k_tubes_tile launch");
+  }
+  for (int j : tubes) {
+    b->desc[j].cur ^= static_cast<int32_t>(((steps[j] + ksteps - 1) / ksteps) & 1);
+    b->t[j] += steps[j];
   }
   return RLB_OK;
 }
@@ -899,6 +1024,10 @@ int rlb_batch_create(rlb_batch **out, const rlb_tube *tubes, int32_t ntubes, int
     d.tau = tubes[j].tau;
     d.eta_s = tubes[j].eta_s;
   }
+  b->flow_fits = true;
+  for (const rlb_tube &t : b->tubes)
+    if (tube_chunks(t.n, precision) > tube_flow_chunks(precision)) b->flow_fits = false;
+  b->tiles = !b->flow_fits || tubes_by_tiles(b->tubes, precision, order);
   b->h_desc = nullptr;
   b->h_order = nullptr;
   b->staged_pending = false;
@@ -978,9 +1107,11 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     if (steps[j] > 0) ++active;
   }
   if (active == 0) return RLB_OK;
-  std::vector<int64_t> rem(steps, steps + b->ntubes);
-  // tests of the stall path bound the kernel's waits to a few polls
+  // tests of the stall path bound the waits of k_tubes to a few polls; where
+  // that is asked for, the batch takes the kernel that waits
   const char *env = std::getenv("RLB_TUBE_SPIN_LIMIT");
+  if (!b->flow_fits || (b->tiles && !env)) return batch_step_tiles(b, steps);
+  std::vector<int64_t> rem(steps, steps + b->ntubes);
   const int32_t spin_limit = env ? std::max(0, std::atoi(env)) : 0;
   for (int j = 0; j < b->ntubes; ++j) b->desc[j].spin_limit = spin_limit;
   // one launch per round: each tube takes as many of its remaining steps as
@@ -988,58 +1119,37 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
   // unless a run is very long)
   for (;;) {
     std::vector<int64_t> now(b->ntubes, 0);
-    std::vector<int> flow, sync;
+    std::vector<int> flow;
     for (int j = 0; j < b->ntubes; ++j) {
       if (rem[j] == 0) continue;
-      const int64_t nch = tube_chunks(b->tubes[j].n, b->precision);
-      if (nch <= tube_flow_chunks(b->precision)) {
-        now[j] = std::min<int64_t>(rem[j], TUBE_ITEMS_MAX / nch);
-        flow.push_back(j);
-      } else {
-        now[j] = rem[j];
-        sync.push_back(j);
-      }
+      now[j] = std::min<int64_t>(rem[j], TUBE_ITEMS_MAX / tube_chunks(b->tubes[j].n, b->precision));
+      flow.push_back(j);
     }
-    if (flow.empty() && sync.empty()) break;
+    if (flow.empty()) break;
     int rc = wait_staged(b);
     if (rc != RLB_OK) return rc;
     // longest work first (cells x steps), ties by index
-    const auto longest = [&](int x, int y) {
+    std::stable_sort(flow.begin(), flow.end(), [&](int x, int y) {
       return static_cast<double>(b->tubes[x].n) * now[x] > static_cast<double>(b->tubes[y].n) * now[y];
-    };
-    std::stable_sort(flow.begin(), flow.end(), longest);
-    std::stable_sort(sync.begin(), sync.end(), longest);
+    });
     for (int j = 0; j < b->ntubes; ++j) {
       b->desc[j].steps = now[j];
       b->h_desc[j] = b->desc[j];
     }
     int k = 0;
     for (int j : flow) b->h_order[k++] = j;
-    for (int j : sync) b->h_order[k++] = j;
     RLB_HIP(hipMemcpyAsync(b->d_desc, b->h_desc, b->ntubes * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, b->stream));
     RLB_HIP(hipMemcpyAsync(b->d_order, b->h_order, k * sizeof(int), hipMemcpyHostToDevice, b->stream));
     RLB_HIP(hipEventRecord(b->staged, b->stream));
     b->staged_pending = true;
-    const int nf = static_cast<int>(flow.size()), ns = static_cast<int>(sync.size());
     with_model(b->order, [&](auto m) {
       using M = decltype(m);
-      if (b->precision == RLB_FP64) {
-        double *pops = reinterpret_cast<double *>(b->pops);
-        if (nf > 0)
-          rlb::k_tubes<M, double><<<dim3(nf), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(pops, b->d_desc, b->d_order,
-                                                                                     b->d_status);
-        if (ns > 0)
-          rlb::k_tubes_sync<M, double><<<dim3(ns), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
-              pops, b->d_desc, b->d_order + nf, b->d_status);
-      } else {
-        float *pops = reinterpret_cast<float *>(b->pops);
-        if (nf > 0)
-          rlb::k_tubes<M, float><<<dim3(nf), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(pops, b->d_desc, b->d_order,
-                                                                                    b->d_status);
-        if (ns > 0)
-          rlb::k_tubes_sync<M, float><<<dim3(ns), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
-              pops, b->d_desc, b->d_order + nf, b->d_status);
-      }
+      if (b->precision == RLB_FP64)
+        rlb::k_tubes<M, double><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
+            reinterpret_cast<double *>(b->pops), b->d_desc, b->d_order, b->d_status);
+      else
+        rlb::k_tubes<M, float><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
+            reinterpret_cast<float *>(b->pops), b->d_desc, b->d_order, b->d_status);
       return 0;
     });
     hipError_t e = hipGetLastError();

@@ -442,8 +442,8 @@ inline constexpr int TUBE_BLOCK = 512; // one workgroup fills a CU at two waves 
 // nearly the same time, so the cache lines they share are fetched once.
 // Every dependence of k is on smaller k, all of which were taken earlier,
 // so the work always progresses.  A step count per chunk is kept modulo
-// 256 (chunks in progress are at most a few steps apart).  Tubes with more
-// chunks than the flag array holds take the barrier form (k_tubes_sync).
+// 256 (chunks in progress are at most a few steps apart).  A batch with a
+// tube of more chunks than the flag array holds takes k_tubes_tile.
 template <class S>
 inline constexpr int TUBE_CHUNK = sizeof(S) == 8 ? 32 : 64;
 // LDS flag bytes: float64 keeps 128 KB for its stash, float32 has no stash
@@ -588,49 +588,6 @@ k_tubes(S *__restrict__ base, const TubeDesc *__restrict__ desc, const int *__re
     // this chunk's stores complete before it is marked done
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) done[c] = static_cast<uint8_t>(st + 1);
-  }
-  if (flags) atomicOr(status + j, flags);
-}
-
-// Tubes beyond TUBE_FLOW_CHUNKS<S> chunks (float64 above 786,432 cells):
-// every step in passes of TB / 2 (float64) or TB (float32) cells, with a
-// workgroup barrier after each step (the step's stores are visible to the
-// next gathers: all wavefronts of a workgroup share one CU).
-template <class M, class S>
-__global__ void __launch_bounds__(TUBE_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
-k_tubes_sync(S *__restrict__ base, const TubeDesc *__restrict__ desc, const int *__restrict__ order,
-             unsigned *__restrict__ status) {
-  constexpr bool f64 = sizeof(S) == 8;
-  constexpr int TB = TUBE_BLOCK;
-  __shared__ S lds[stash_rows<M, S>][f64 ? TB : 1];
-  const int j = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
-  const TubeDesc d = desc[j];
-  Geom g;
-  g.nx = 1;
-  g.ny = 1;
-  g.nz = d.n;
-  g.cells = d.n;
-  Relax rx;
-  rx.mode = d.mode;
-  rx.tau = d.tau;
-  rx.eta_s = d.eta_s;
-  constexpr int per_pass = f64 ? TB / 2 : TB;
-  const int slot = f64 ? (static_cast<int>(threadIdx.x) >> 6) * 32 + (threadIdx.x & 31) : static_cast<int>(threadIdx.x);
-  const int wave0 = f64 ? (static_cast<int>(threadIdx.x) >> 6) * 32 : (static_cast<int>(threadIdx.x) & ~63);
-  unsigned flags = 0;
-  int cur = d.cur;
-  for (int64_t st = 0; st < d.steps; ++st) {
-    const S *in = base + (cur ? d.off[1] : d.off[0]);
-    S *out = base + (cur ? d.off[0] : d.off[1]);
-    for (int c0 = 0; c0 < d.n; c0 += per_pass) {
-      if (c0 + wave0 >= d.n) continue; // wavefronts wholly beyond the tube skip the pass
-      if constexpr (f64)
-        pair_cell_step<M, S, TB>(in, out, g, rx, c0 + slot, lds, flags);
-      else
-        tube_cell_step<M, S>(in, out, g, rx, c0 + slot, flags);
-    }
-    __syncthreads();
-    cur ^= 1;
   }
   if (flags) atomicOr(status + j, flags);
 }
