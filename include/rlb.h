@@ -253,16 +253,16 @@ int rlb_set_walls(rlb_solver *s, const uint8_t *solid, void *d_buf, size_t bytes
  * The Riemann problems of Sec. III are one-dimensional: a tube is a periodic
  * 1 x 1 x n lattice on which only the z displacement of each point moves
  * anything.  A batch holds many tubes of one precision in one caller-owned
- * buffer and advances all of them together.  Many tubes take one persistent
- * launch: one workgroup per tube, launched longest-work-first, whose
+ * buffer and advances all of them together: launches of up to five steps
+ * spread the cells over the chip, 64 lanes to a workgroup.  Many third-order
+ * mixed-precision tubes (some 300 or more; same results) take one persistent
+ * launch instead: one workgroup per tube, launched longest-work-first, whose
  * wavefronts take the tube's (step, chunk) work in order and wait only for
  * the neighbouring chunks' previous step.  Every such wait is bounded: after
  * about 0.1 s it gives up and raises RLB_FLAG_STALL in its tube (never
  * expected; the environment variable RLB_TUBE_SPIN_LIMIT, read by
  * rlb_batch_step, lowers the bound to that many polls, for tests of that
- * path, and selects this kernel).  Few tubes, or a float64 tube above 786,432
- * cells, are spread over the chip instead, by launches of up to five steps.
- * The choice is made at creation from the tubes' lengths.  Tubes never
+ * path, and selects this kernel for any number of such tubes).  Tubes never
  * interact; a failure (status flag) stays in its tube. */
 typedef struct rlb_tube {
   int32_t n;        /* cells along z, 1 .. 4,194,304 (2^22)                */
@@ -319,10 +319,9 @@ void rlb_batch_destroy(rlb_batch *b);
  * chunk_steps launches; the last issue may end with fewer; a long tube run
  * as a box by chunk_steps * max(1, 262144 / nz)), or each of its
  * tubes by max(chunk_steps, chunk_steps * 8192 / nz) steps, all resident
- * tubes of one precision and model in one persistent launch.  Tubes of 2048
- * cells or more run as 1 x 1 x nz boxes (box kernels, which spread a step
- * over many CUs, where a persistent tube launch gives a tube one CU), on
- * the tube stream of their precision.
+ * tubes of one precision and model together, as in a batch.  Mixed-precision
+ * tubes of 2048 cells or more run as 1 x 1 x nz boxes (box kernels), on the
+ * tube stream of their precision.
  * The four streams should each have a hardware queue: a process that has
  * other busy streams should raise GPU_MAX_HW_QUEUES (HIP's default is 4).
  * A request's result does not depend on what else is resident (the kernels

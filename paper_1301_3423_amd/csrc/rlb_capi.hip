@@ -780,8 +780,6 @@ struct rlb_batch {
   int *h_order;
   hipEvent_t staged;
   bool staged_pending;
-  bool flow_fits; // k_tubes has flags for every tube's chunks
-  bool tiles;     // stepped by k_tubes_tile rather than k_tubes
 };
 
 namespace {
@@ -795,15 +793,9 @@ bool valid_tube(const rlb_tube &tb) {
   return false;
 }
 
-// Chunks of one wavefront in the tube kernel, the most a workgroup's flags
-// hold, and the most (step, chunk) items one launch gives a tube.
-int64_t tube_chunks(int32_t n, int precision) {
-  const int ch = precision == RLB_FP64 ? rlb::TUBE_CHUNK<double> : rlb::TUBE_CHUNK<float>;
-  return (static_cast<int64_t>(n) + ch - 1) / ch;
-}
-int64_t tube_flow_chunks(int precision) {
-  return precision == RLB_FP64 ? rlb::TUBE_FLOW_CHUNKS<double> : rlb::TUBE_FLOW_CHUNKS<float>;
-}
+// Chunks of one wavefront in k_tubes, and the most (step, chunk) items one
+// launch gives a tube.
+int64_t tube_chunks(int32_t n) { return (static_cast<int64_t>(n) + rlb::TUBE_CHUNK - 1) / rlb::TUBE_CHUNK; }
 constexpr int64_t TUBE_ITEMS_MAX = (int64_t(1) << 31) - 1;
 
 size_t batch_header_bytes(int ntubes) {
@@ -835,124 +827,127 @@ int wait_staged(rlb_batch *b) {
   return RLB_OK;
 }
 
-// What a step of a batch takes, in us, by kernel: one persistent workgroup
-// per tube (k_tubes) or launches of k steps over 64-lane tiles
-// (k_tubes_tile), from measurements of 1 to 512 tubes of 1 to 4000 cells.
-struct TubeCost {
-  double flow, flow_cell; // the longest tube: flow + flow_cell * cells
-  double flow_rate;       // cells per us with every CU at work
-  double start, step;     // a launch of k steps: start + k * step, or, with
-  double load, work;      // tiles to spare, tiles / 256 * (load + k * work)
+// What launches of k_tubes_tile take, in us, from measurements of 1 to 512
+// tubes of 1 to 4000 cells: one of k steps start + k * step, or, with tiles
+// to spare, start + tiles / 256 * (load + k * work).
+struct TileCost {
+  double start, step, load, work;
+  double launches(int k, double launches, double tiles) const {
+    return launches * start + std::max(launches * k * step, tiles / 256 * (load + k * work));
+  }
 };
-TubeCost tube_cost(int precision, int order) {
-  if (order == RLB_ORDER2)
-    return precision == RLB_FP64 ? TubeCost{3.5, 1.0 / 43, 5000, 3.0, 3.0, 3.4, 1.65}
-                                 : TubeCost{4.0, 1.0 / 90, 10000, 2.5, 2.9, 2.2, 1.75};
-  return precision == RLB_FP64 ? TubeCost{7.0, 1.0 / 21, 2520, 3.5, 4.4, 6.5, 3.6}
-                               : TubeCost{7.0, 1.0 / 45, 5050, 2.9, 4.1, 3.0, 2.6};
+// The kernel's forms: cells split over NSHELL wavefronts (the shortest
+// chain), or, in float32 with its same bits, over two (third order) or one
+// (second order), which repeat less of the frame's arithmetic.
+struct TileForm {
+  bool wide;
+  TileCost cost;
+};
+std::vector<TileForm> tile_forms(int precision, int order) {
+  if (precision == RLB_FP64)
+    return {{false, order == RLB_ORDER2 ? TileCost{3.0, 3.4, 3.2, 1.7} : TileCost{3.5, 4.4, 5.4, 2.6}}};
+  if (order == RLB_ORDER2) return {{false, {2.8, 3.3, 2.0, 1.3}}, {true, {2.6, 3.9, 1.6, 0.75}}};
+  return {{false, {2.9, 4.1, 3.4, 2.4}}, {true, {3.2, 6.0, 3.3, 1.8}}};
 }
 
 int64_t tube_tiles(int32_t n, int k) { return (n + rlb::tube_tile_cells(k) - 1) / rlb::tube_tile_cells(k); }
 
-// Time of `launches` launches of k steps that take `tiles` tiles in all.
-double tile_time(const TubeCost &c, int k, double launches, double tiles) {
-  return launches * c.start + std::max(launches * k * c.step, tiles / 256 * (c.load + k * c.work));
-}
+// A tube to advance: its descriptor (off, n, cur, mode, tau, eta_s), where
+// its status word lies, and how many steps.
+struct TubeJob {
+  rlb::TubeDesc d;
+  int status;
+  int64_t steps;
+};
 
-// Whether the tubes are stepped by tiles: from their lengths alone, so that
-// every step of a batch takes the same kernel.  Few tubes, or tubes of very
-// uneven length, leave most CUs without a workgroup of k_tubes; with some
-// 300 tubes or more the persistent kernel, which splits no cell and computes
-// none twice, is the faster (512 tubes of 200-4000 cells: 433 against 526 us
-// per step in float64, 216 against 278 in mixed precision).
-bool tubes_by_tiles(const std::vector<rlb_tube> &tubes, int precision, int order) {
-  const TubeCost c = tube_cost(precision, order);
-  double cells = 0.0;
-  int32_t longest = 0;
-  for (const rlb_tube &t : tubes) {
-    cells += t.n;
-    longest = std::max(longest, t.n);
-  }
-  const double flow = std::max(c.flow + c.flow_cell * longest, cells / c.flow_rate);
-  for (int k = 1; k <= rlb::TUBE_MAX_KSTEPS; ++k) {
-    double tiles = 0.0;
-    for (const rlb_tube &t : tubes) tiles += static_cast<double>(tube_tiles(t.n, k));
-    if (tile_time(c, k, 1.0, tiles) < flow * k) return true;
-  }
-  return false;
-}
+struct TilePlan {
+  int ksteps;
+  bool wide;
+  double time; // estimate, us
+};
 
-// Steps per launch for this call: the k of least estimated time.
-int tile_steps(const rlb_batch *b, const int64_t *steps) {
-  const TubeCost c = tube_cost(b->precision, b->order);
-  int best = 1;
-  double best_time = 0.0;
-  for (int k = 1; k <= rlb::TUBE_MAX_KSTEPS; ++k) {
-    double launches = 0.0, tiles = 0.0;
-    for (int j = 0; j < b->ntubes; ++j) {
-      const double l = static_cast<double>((steps[j] + k - 1) / k);
-      launches = std::max(launches, l);
-      tiles += l * static_cast<double>(tube_tiles(b->tubes[j].n, k));
+// The form and the steps per launch of least estimated time.
+TilePlan plan_tiles(const std::vector<TubeJob> &jobs, int precision, int order) {
+  TilePlan best{1, false, -1.0};
+  for (const TileForm &f : tile_forms(precision, order))
+    for (int k = 1; k <= rlb::TUBE_MAX_KSTEPS; ++k) {
+      double launches = 0.0, tiles = 0.0;
+      for (const TubeJob &j : jobs) {
+        const double l = static_cast<double>((j.steps + k - 1) / k);
+        launches = std::max(launches, l);
+        tiles += l * static_cast<double>(tube_tiles(j.d.n, k));
+      }
+      const double t = f.cost.launches(k, launches, tiles);
+      if (best.time < 0.0 || t < best.time) best = {k, f.wide, t};
     }
-    const double t = tile_time(c, k, launches, tiles);
-    if (k == 1 || t < best_time) {
-      best = k;
-      best_time = t;
-    }
-  }
   return best;
 }
 
-// Advances the tubes by launches of k_tubes_tile, the tubes with the most
-// steps first, so that those which have finished drop off the grid's end.
-int batch_step_tiles(rlb_batch *b, const int64_t *steps) {
-  const int ksteps = tile_steps(b, steps);
-  std::vector<int> tubes;
-  for (int j = 0; j < b->ntubes; ++j)
-    if (steps[j] > 0) tubes.push_back(j);
-  std::stable_sort(tubes.begin(), tubes.end(), [&](int x, int y) { return steps[x] > steps[y]; });
-  int rc = wait_staged(b);
-  if (rc != RLB_OK) return rc;
-  const int nt = static_cast<int>(tubes.size());
-  std::vector<int> tiles_up_to(nt);
-  int tiles = 0;
-  for (int k = 0; k < nt; ++k) {
-    const int j = tubes[k];
-    b->h_desc[k] = b->desc[j];
-    b->h_desc[k].steps = steps[j];
-    b->h_desc[k].spin_limit = tiles;
-    b->h_order[k] = j;
-    tiles += static_cast<int>(tube_tiles(b->tubes[j].n, ksteps));
-    tiles_up_to[k] = tiles;
+// Whether the one-workgroup-per-tube kernel takes less time.  It exists for
+// third-order float32, whose results are the same bits either way: with some
+// 300 tubes or more it keeps every CU at work and computes no cell twice
+// (512 tubes of 200-4000 cells: 217 us per step against 233 by tiles; 96 of
+// them 112 against 50).
+bool flow_is_faster(const std::vector<TubeJob> &jobs, const TilePlan &plan) {
+  double longest = 0.0, all = 0.0;
+  for (const TubeJob &j : jobs) {
+    longest = std::max(longest, (7.0 + j.d.n / 45.0) * static_cast<double>(j.steps));
+    all += static_cast<double>(j.d.n) * static_cast<double>(j.steps) / 5050.0;
   }
-  RLB_HIP(hipMemcpyAsync(b->d_desc, b->h_desc, nt * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, b->stream));
-  RLB_HIP(hipMemcpyAsync(b->d_order, b->h_order, nt * sizeof(int), hipMemcpyHostToDevice, b->stream));
-  RLB_HIP(hipEventRecord(b->staged, b->stream));
-  b->staged_pending = true;
-  int live = nt;
-  for (int round = 0; live > 0; ++round) {
-    while (live > 0 && steps[tubes[live - 1]] <= static_cast<int64_t>(round) * ksteps) --live;
+  return std::max(longest, all) < plan.time;
+}
+
+template <class M, class S, int NG>
+void launch_tiles(dim3 grid, void *pops, const rlb::TubeDesc *desc, const int *first, int ntubes, int round, int ksteps,
+                  unsigned *status, hipStream_t st) {
+  rlb::k_tubes_tile<M, S, NG><<<grid, dim3(64 * NG), 0, st>>>(static_cast<S *>(pops), desc, first, ntubes, round,
+                                                              ksteps, status);
+}
+
+// Advances the jobs by launches of k_tubes_tile, the tubes with the most
+// steps first, so that those which have finished drop off the grid's end.
+// h_desc, h_first: pinned staging for the jobs' tables, free for the next use
+// once `staged` (if given) has passed; the caller flips each job's current
+// buffer when (steps + ksteps - 1) / ksteps is odd.
+int run_tiles(std::vector<TubeJob> &jobs, const TilePlan &plan, int precision, int order, void *pops,
+              rlb::TubeDesc *h_desc, int *h_first, rlb::TubeDesc *d_desc, int *d_first, unsigned *d_status,
+              hipStream_t st, hipEvent_t staged) {
+  const int k = plan.ksteps;
+  std::stable_sort(jobs.begin(), jobs.end(), [](const TubeJob &x, const TubeJob &y) { return x.steps > y.steps; });
+  const size_t nt = jobs.size();
+  int tiles = 0;
+  for (size_t i = 0; i < nt; ++i) {
+    h_desc[i] = jobs[i].d;
+    h_desc[i].steps = jobs[i].steps;
+    h_desc[i].spin_limit = jobs[i].status;
+    h_first[i] = tiles;
+    tiles += static_cast<int>(tube_tiles(jobs[i].d.n, k));
+  }
+  RLB_HIP(hipMemcpyAsync(d_desc, h_desc, nt * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
+  RLB_HIP(hipMemcpyAsync(d_first, h_first, nt * sizeof(int), hipMemcpyHostToDevice, st));
+  if (staged) RLB_HIP(hipEventRecord(staged, st));
+  size_t live = nt;
+  for (int round = 0;; ++round) {
+    while (live > 0 && jobs[live - 1].steps <= static_cast<int64_t>(round) * k) {
+      --live;
+      tiles -= static_cast<int>(tube_tiles(jobs[live].d.n, k));
+    }
     if (live == 0) break;
-    with_model(b->order, [&](auto m) {
+    with_model(order, [&](auto m) {
       using M = decltype(m);
-      const auto launch = [&](auto zero) {
-        using S = decltype(zero);
-        constexpr int NG = rlb::Split<M, S>::NG;
-        rlb::k_tubes_tile<M, S><<<dim3(tiles_up_to[live - 1]), dim3(64 * NG), 0, b->stream>>>(
-            reinterpret_cast<S *>(b->pops), b->d_desc, b->d_order, live, round, ksteps, b->d_status);
+      const auto go = [&](auto kernel) {
+        kernel(dim3(tiles), pops, d_desc, d_first, static_cast<int>(live), round, k, d_status, st);
       };
-      if (b->precision == RLB_FP64)
-        launch(0.0);
+      if (precision == RLB_FP64)
+        go(launch_tiles<M, double, M::NSHELL>);
+      else if (plan.wide)
+        go(launch_tiles<M, float, M::ORDER == 3 ? 2 : 1>);
       else
-        launch(0.0f);
+        go(launch_tiles<M, float, M::NSHELL>);
       return 0;
     });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_tubes_tile launch");
-  }
-  for (int j : tubes) {
-    b->desc[j].cur ^= static_cast<int32_t>(((steps[j] + ksteps - 1) / ksteps) & 1);
-    b->t[j] += steps[j];
   }
   return RLB_OK;
 }
@@ -1024,10 +1019,6 @@ int rlb_batch_create(rlb_batch **out, const rlb_tube *tubes, int32_t ntubes, int
     d.tau = tubes[j].tau;
     d.eta_s = tubes[j].eta_s;
   }
-  b->flow_fits = true;
-  for (const rlb_tube &t : b->tubes)
-    if (tube_chunks(t.n, precision) > tube_flow_chunks(precision)) b->flow_fits = false;
-  b->tiles = !b->flow_fits || tubes_by_tiles(b->tubes, precision, order);
   b->h_desc = nullptr;
   b->h_order = nullptr;
   b->staged_pending = false;
@@ -1107,10 +1098,30 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     if (steps[j] > 0) ++active;
   }
   if (active == 0) return RLB_OK;
+  std::vector<TubeJob> jobs;
+  bool flow = b->precision == RLB_MIXED && b->order == RLB_ORDER3;
+  for (int j = 0; j < b->ntubes; ++j) {
+    if (steps[j] == 0) continue;
+    jobs.push_back({b->desc[j], j, steps[j]});
+    flow = flow && tube_chunks(b->tubes[j].n) <= rlb::TUBE_FLOW_CHUNKS;
+  }
   // tests of the stall path bound the waits of k_tubes to a few polls; where
   // that is asked for, the batch takes the kernel that waits
   const char *env = std::getenv("RLB_TUBE_SPIN_LIMIT");
-  if (!b->flow_fits || (b->tiles && !env)) return batch_step_tiles(b, steps);
+  const TilePlan plan = plan_tiles(jobs, b->precision, b->order);
+  if (!flow || !(env || flow_is_faster(jobs, plan))) {
+    int rc = wait_staged(b);
+    if (rc != RLB_OK) return rc;
+    b->staged_pending = true;
+    rc = run_tiles(jobs, plan, b->precision, b->order, b->pops, b->h_desc, b->h_order, b->d_desc, b->d_order,
+                   b->d_status, b->stream, b->staged);
+    if (rc != RLB_OK) return rc;
+    for (int j = 0; j < b->ntubes; ++j) {
+      b->desc[j].cur ^= static_cast<int32_t>(((steps[j] + plan.ksteps - 1) / plan.ksteps) & 1);
+      b->t[j] += steps[j];
+    }
+    return RLB_OK;
+  }
   std::vector<int64_t> rem(steps, steps + b->ntubes);
   const int32_t spin_limit = env ? std::max(0, std::atoi(env)) : 0;
   for (int j = 0; j < b->ntubes; ++j) b->desc[j].spin_limit = spin_limit;
@@ -1122,7 +1133,7 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     std::vector<int> flow;
     for (int j = 0; j < b->ntubes; ++j) {
       if (rem[j] == 0) continue;
-      now[j] = std::min<int64_t>(rem[j], TUBE_ITEMS_MAX / tube_chunks(b->tubes[j].n, b->precision));
+      now[j] = std::min<int64_t>(rem[j], TUBE_ITEMS_MAX / tube_chunks(b->tubes[j].n));
       flow.push_back(j);
     }
     if (flow.empty()) break;
@@ -1142,16 +1153,8 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     RLB_HIP(hipMemcpyAsync(b->d_order, b->h_order, k * sizeof(int), hipMemcpyHostToDevice, b->stream));
     RLB_HIP(hipEventRecord(b->staged, b->stream));
     b->staged_pending = true;
-    with_model(b->order, [&](auto m) {
-      using M = decltype(m);
-      if (b->precision == RLB_FP64)
-        rlb::k_tubes<M, double><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
-            reinterpret_cast<double *>(b->pops), b->d_desc, b->d_order, b->d_status);
-      else
-        rlb::k_tubes<M, float><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
-            reinterpret_cast<float *>(b->pops), b->d_desc, b->d_order, b->d_status);
-      return 0;
-    });
+    rlb::k_tubes<<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(reinterpret_cast<float *>(b->pops), b->d_desc,
+                                                                   b->d_order, b->d_status);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_tubes launch");
     for (int j = 0; j < b->ntubes; ++j) {
@@ -1323,17 +1326,16 @@ int64_t request_cells(const rlb_request &r) {
   return static_cast<int64_t>(r.nx) * r.ny * r.nz;
 }
 
-// Tubes of at least this many cells run as 1 x 1 x n boxes (still on the
-// tube stream of their precision): the box kernels spread a step over n / 64
-// workgroups (many CUs), where the persistent tube launch gives each tube one
-// CU (about 8 MLUPS in float64, so a tube of 8000 cells and 2000 steps would
-// take 2 s).
+// Mixed-precision tubes of at least this many cells run as 1 x 1 x n boxes
+// (still on the tube stream of their precision); their results are those of
+// the box kernels' rounding.
 constexpr int32_t TUBE_AS_BOX_CELLS = 2048;
 
-bool runs_as_box(const rlb_request &r) { return r.kind == RLB_REQ_BOX || r.nz >= TUBE_AS_BOX_CELLS; }
-// the server's tubes always fit the dataflow form of the tube kernel
-static_assert(TUBE_AS_BOX_CELLS / rlb::TUBE_CHUNK<double> <= rlb::TUBE_FLOW_CHUNKS<double> &&
-              TUBE_AS_BOX_CELLS / rlb::TUBE_CHUNK<float> <= rlb::TUBE_FLOW_CHUNKS<float>);
+bool runs_as_box(const rlb_request &r) {
+  return r.kind == RLB_REQ_BOX || (r.precision == RLB_MIXED && r.nz >= TUBE_AS_BOX_CELLS);
+}
+// the server's mixed tubes always fit the flags of k_tubes
+static_assert(TUBE_AS_BOX_CELLS / rlb::TUBE_CHUNK <= rlb::TUBE_FLOW_CHUNKS);
 
 bool request_valid(const rlb_request &r, std::string &why) {
   if (r.kind != RLB_REQ_TUBE && r.kind != RLB_REQ_BOX) return why = "bad kind", false;
@@ -1569,13 +1571,13 @@ constexpr int64_t TUBE_ROUND_CELLS = 8192;
 
 int64_t tube_round_steps(const rlb_server *sv, const ServeReq *q) {
   const int64_t budget = static_cast<int64_t>(sv->chunk) * TUBE_ROUND_CELLS / std::max<int64_t>(q->r.nz, 1);
-  // the tube kernel counts a launch's (step, chunk) items in 32 bits
-  const int64_t cap = TUBE_ITEMS_MAX / tube_chunks(q->r.nz, q->r.precision);
+  // k_tubes counts a launch's (step, chunk) items in 32 bits
+  const int64_t cap = TUBE_ITEMS_MAX / tube_chunks(q->r.nz);
   return std::min<int64_t>(std::min<int64_t>(q->remaining, cap), std::max<int64_t>(sv->chunk, budget));
 }
 
 int tubes_advance(rlb_server *sv, int prec, int order, bool &issued) {
-  // all resident tubes of this precision and model, one persistent launch
+  // all resident tubes of this precision and model together
   std::vector<ServeReq *> tubes;
   for (ServeReq *q : sv->resident)
     if (!runs_as_box(q->r) && q->r.precision == prec && norm_order(q->r.order) == order && q->remaining > 0)
@@ -1587,38 +1589,49 @@ int tubes_advance(rlb_server *sv, int prec, int order, bool &issued) {
     return static_cast<double>(a->r.nz) * tube_round_steps(sv, a) >
            static_cast<double>(b->r.nz) * tube_round_steps(sv, b);
   });
-  int k = 0;
+  std::vector<TubeJob> jobs;
   for (ServeReq *q : tubes) {
-    rlb::TubeDesc &d = sv->h_desc[p][q->slot];
-    d.off[0] = q->tube_off[0];
-    d.off[1] = q->tube_off[1];
-    d.steps = tube_round_steps(sv, q);
-    d.n = q->r.nz;
-    d.cur = q->cur;
-    d.mode = q->r.tau_mode == RLB_TAU_ETA_S ? 1 : 0;
-    d.spin_limit = 0;
-    d.tau = q->r.tau;
-    d.eta_s = q->r.eta_s;
-    sv->h_order[p][k++] = q->slot;
+    TubeJob job;
+    job.d.off[0] = q->tube_off[0];
+    job.d.off[1] = q->tube_off[1];
+    job.d.n = q->r.nz;
+    job.d.cur = q->cur;
+    job.d.mode = q->r.tau_mode == RLB_TAU_ETA_S ? 1 : 0;
+    job.d.spin_limit = 0;
+    job.d.tau = q->r.tau;
+    job.d.eta_s = q->r.eta_s;
+    job.status = q->slot;
+    job.steps = tube_round_steps(sv, q);
+    job.d.steps = job.steps;
+    jobs.push_back(job);
   }
   hipStream_t st = sv->streams[tube_stream(p)];
-  RLB_HIP(hipMemcpyAsync(sv->d_desc[p], sv->h_desc[p], sv->max_tubes * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
-  RLB_HIP(hipMemcpyAsync(sv->d_order[p], sv->h_order[p], k * sizeof(int), hipMemcpyHostToDevice, st));
-  with_model(order, [&](auto m) {
-    using M = decltype(m);
-    if (prec == RLB_FP64)
-      rlb::k_tubes<M, double><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, st>>>(reinterpret_cast<double *>(sv->pool),
-                                                                          sv->d_desc[p], sv->d_order[p], sv->d_status);
-    else
-      rlb::k_tubes<M, float><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, st>>>(reinterpret_cast<float *>(sv->pool),
-                                                                         sv->d_desc[p], sv->d_order[p], sv->d_status);
-    return 0;
-  });
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "serve k_tubes");
+  // float64 and the second-order model always go by tiles, so that a result
+  // does not depend on what else is resident; third-order float32 has the
+  // same bits either way
+  const TilePlan plan = plan_tiles(jobs, prec, order);
+  int64_t per_launch = 1; // steps after which a tube's buffers change places
+  if (prec == RLB_MIXED && order == RLB_ORDER3 && flow_is_faster(jobs, plan)) {
+    int k = 0;
+    for (const TubeJob &job : jobs) {
+      sv->h_desc[p][job.status] = job.d;
+      sv->h_order[p][k++] = job.status;
+    }
+    RLB_HIP(hipMemcpyAsync(sv->d_desc[p], sv->h_desc[p], sv->max_tubes * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
+    RLB_HIP(hipMemcpyAsync(sv->d_order[p], sv->h_order[p], k * sizeof(int), hipMemcpyHostToDevice, st));
+    rlb::k_tubes<<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, st>>>(reinterpret_cast<float *>(sv->pool), sv->d_desc[p],
+                                                            sv->d_order[p], sv->d_status);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "serve k_tubes");
+  } else {
+    const int rc = run_tiles(jobs, plan, prec, order, sv->pool, sv->h_desc[p], sv->h_order[p], sv->d_desc[p],
+                             sv->d_order[p], sv->d_status, st, nullptr);
+    if (rc != RLB_OK) return rc;
+    per_launch = plan.ksteps;
+  }
   for (ServeReq *q : tubes) {
     const int64_t s = tube_round_steps(sv, q);
-    q->cur ^= static_cast<int>(s & 1);
+    q->cur ^= static_cast<int>(((s + per_launch - 1) / per_launch) & 1);
     q->remaining -= s;
   }
   return RLB_OK;

@@ -453,28 +453,49 @@ struct MJ {
   }
 };
 
+__device__ __forceinline__ MJ mj_of(double n, double T, double U0, double Ux, double Uy, double Uz) {
+  return MJ{n, n * T, 4.0 * n * T * T, n / (2.0 * T), {U0, Ux, Uy, Uz}};
+}
+
+// The coefficients of one parity block: c[j - begin] for its monomials j.
+template <class M, int BLK>
+struct EqBlock {
+  double c[M::BLOCK_BEGIN[BLK + 1] - M::BLOCK_BEGIN[BLK]];
+};
+
+template <class M, int BLK>
+__device__ __forceinline__ EqBlock<M, BLK> eq_block(const MJ &mj) {
+  constexpr int b0 = M::BLOCK_BEGIN[BLK], b1 = M::BLOCK_BEGIN[BLK + 1];
+  EqBlock<M, BLK> e;
+  double Mb[b1 - b0];
+  static_for<b0, b1>([&](auto J) {
+    constexpr int j = decltype(J)::value;
+    constexpr Mono mo = M::MONO[j];
+    Mb[j - b0] = mj.template moment<mo.a0, mo.ax, mo.ay, mo.az>();
+  });
+  static_for<b0, b1>([&](auto A) {
+    constexpr int ia = decltype(A)::value;
+    double acc = 0.0;
+    static_for<b0, b1>([&](auto J) {
+      constexpr int j = decltype(J)::value;
+      if constexpr (M::GINV[ia][j] != 0.0) acc = __builtin_fma(M::GINV[ia][j], Mb[j - b0], acc);
+    });
+    e.c[ia - b0] = acc;
+  });
+  return e;
+}
+
 template <class M>
 __device__ __forceinline__ EqCoef<M> eq_coefficients(double n, double T, double U0, double Ux, double Uy,
                                                      double Uz) {
-  const MJ mj{n, n * T, 4.0 * n * T * T, n / (2.0 * T), {U0, Ux, Uy, Uz}};
+  const MJ mj = mj_of(n, T, U0, Ux, Uy, Uz);
   EqCoef<M> e;
   static_for<0, M::NBLOCK>([&](auto B) {
     constexpr int blk = decltype(B)::value;
-    constexpr int b0 = M::BLOCK_BEGIN[blk], b1 = M::BLOCK_BEGIN[blk + 1];
-    double Mb[b1 - b0];
-    static_for<b0, b1>([&](auto J) {
+    const EqBlock<M, blk> b = eq_block<M, blk>(mj);
+    static_for<M::BLOCK_BEGIN[blk], M::BLOCK_BEGIN[blk + 1]>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      constexpr Mono mo = M::MONO[j];
-      Mb[j - b0] = mj.template moment<mo.a0, mo.ax, mo.ay, mo.az>();
-    });
-    static_for<b0, b1>([&](auto A) {
-      constexpr int ia = decltype(A)::value;
-      double acc = 0.0;
-      static_for<b0, b1>([&](auto J) {
-        constexpr int j = decltype(J)::value;
-        if constexpr (M::GINV[ia][j] != 0.0) acc = __builtin_fma(M::GINV[ia][j], Mb[j - b0], acc);
-      });
-      e.c[ia] = acc;
+      e.c[j] = b.c[j - M::BLOCK_BEGIN[blk]];
     });
   });
   return e;
@@ -539,26 +560,41 @@ constexpr double inv_r_pow(int e) {
   return e == 0 ? 1.0 : e == 1 ? M::INV_R : e == 2 ? M::INV_R2 : M::INV_R3;
 }
 
+// The parity block that holds the monomials of spatial part si.
+template <class M>
+constexpr int spatial_block(int si) {
+  for (int b = 0; b < M::NBLOCK; ++b)
+    for (int j = M::BLOCK_BEGIN[b]; j < M::BLOCK_BEGIN[b + 1]; ++j)
+      if (SPATIAL<M>.of[j] == si) return b;
+  return -1;
+}
+
+// Coefficient of spatial part SI in the theta-polynomial of shell L, from
+// the basis coefficients c of the monomials [B0, B1) that hold all of its
+// terms, accumulated from the highest energy power down.
+template <class M, int L, int SI, int B0, int B1>
+__device__ __forceinline__ double spatial_coefficient(const double (&c)[B1 - B0]) {
+  constexpr double p = shell_p0<M>(L);
+  double acc = 0.0;
+  static_for<B0, B1>([&](auto J) {
+    constexpr int j = B0 + B1 - 1 - decltype(J)::value;
+    if constexpr (SPATIAL<M>.of[j] == SI) {
+      constexpr Mono mo = M::MONO[j];
+      constexpr int sd = mo.ax + mo.ay + mo.az;
+      constexpr double k = ipow(p, mo.a0 + sd) * inv_r_pow<M>(sd);
+      acc = __builtin_fma(k, c[j - B0], acc);
+    }
+  });
+  return acc;
+}
+
 // Coefficients of the theta-polynomial of shell L, rounded once to CT.
-// The terms of one spatial part are accumulated from the highest energy
-// power down.
 template <class M, int L, class CT>
 __device__ __forceinline__ ShellCoef<M, CT> shell_coefficients(const EqCoef<M> &e) {
-  constexpr double p = shell_p0<M>(L);
   ShellCoef<M, CT> s;
   static_for<0, SpatialTable<M>::NS>([&](auto Sx) {
     constexpr int si = decltype(Sx)::value;
-    double acc = 0.0;
-    static_for<0, M::NM>([&](auto J) {
-      constexpr int j = M::NM - 1 - decltype(J)::value;
-      if constexpr (SPATIAL<M>.of[j] == si) {
-        constexpr Mono mo = M::MONO[j];
-        constexpr int sd = mo.ax + mo.ay + mo.az;
-        constexpr double k = ipow(p, mo.a0 + sd) * inv_r_pow<M>(sd);
-        acc = __builtin_fma(k, e.c[j], acc);
-      }
-    });
-    s.c[si] = CT(acc);
+    s.c[si] = CT(spatial_coefficient<M, L, si, 0, M::NM>(e.c));
   });
   return s;
 }
