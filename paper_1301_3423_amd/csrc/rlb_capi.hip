@@ -149,6 +149,18 @@ int access_of(const rlb_solver *s) {
   return (s->t & 1) ? rlb::AA_ODD : rlb::AA_EVEN;
 }
 
+// Whether float32 rows that are no whole number of wavefronts take the
+// one-lane kernel (k_step_any) rather than the two-lane one, whose bits are
+// the same: from the size where its longer chain per wavefront no longer
+// shows (us per step, two-lane / one-lane; third order: 20^3 11.2 / 13.2,
+// 48^3 31.0 / 31.9, 60^3 56.1 / 55.1, 101^3 229 / 203, 200^3 1622 / 1417; second
+// order: 33^3 10.9 / 11.8, 48^3 17.0 / 16.7, 60^3 31.8 / 28.5, 101^3 131 / 107)
+// up to the 4 GiB its 32-bit offsets reach.
+template <class M>
+bool any_kernel_fits(int64_t cells) {
+  return cells >= (M::ORDER == 3 ? 196608 : 98304) && rlb::tile_bytes32_fit<M, float>(cells);
+}
+
 // The step kernels of one box, with or without walls, for access AC (with
 // AA the input and output buffer is the same).
 template <class M, bool WALLS, int AC>
@@ -177,6 +189,11 @@ void launch_step_kernels(rlb_solver *s, const rlb::Geom &g, const rlb::Relax &r)
       rlb::k_step_row<M, float, WALLS, AC><<<grid, block, 0, s->stream>>>(
           static_cast<const float *>(in), static_cast<float *>(out), g, r, s->status, solid);
     }
+  } else if (AC == rlb::PULL && any_kernel_fits<M>(s->cells)) {
+    constexpr int RB = rlb::step_block<rlb::PULL>;
+    const dim3 grid(static_cast<unsigned>((s->cells + RB - 1) / RB)), block(RB);
+    rlb::k_step_any<M, WALLS><<<grid, block, 0, s->stream>>>(static_cast<const float *>(in), static_cast<float *>(out),
+                                                             g, r, s->status, solid);
   } else {
     constexpr int TB = rlb::pair_block<M, float, AC>;
     const dim3 grid(static_cast<unsigned>((s->cells + TB / 2 - 1) / (TB / 2))), block(TB);

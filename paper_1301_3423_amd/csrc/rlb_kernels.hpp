@@ -734,6 +734,117 @@ k_step_row(InPtr<S, AC> cur, OutPtr<S, AC> nxt, Geom g, Relax rx, unsigned *__re
   if (active && flags) atomicOr(status, flags);
 }
 
+// ---- the float32 time step of other boxes: one cell per lane --------------
+//
+// Rows that are no whole number of wavefronts: a wavefront takes 64
+// consecutive cells of the lattice, whatever rows they lie in, and every lane
+// forms its own offsets (32-bit, so buffers below 4 GiB).  The operations on
+// each population are those of the two-lane kernel (k_step), which steps the
+// smallest boxes and those beyond 4 GiB, in the same order, so the two give
+// the same bits: the moments of the members 2k and of the members 2k + 1 are
+// summed apart and added at the end, and f^eq = w (E +- O).  Per 64 cells it
+// issues 5400 vector instructions where two wavefronts of the two-lane kernel
+// issue 8600, which was what bounded them: 101^3 229 -> 203 us per step
+// (4.6 -> 5.2 TB/s), 200^3 1622 -> 1417 us (5.1 -> 5.8 TB/s, HBM).
+
+// The two halves of the moments, as the two lanes of k_step form them.
+template <class M, class S>
+__device__ __forceinline__ Moments moments_by_member(const S (&f)[M::Q]) {
+  Moments h[2];
+  static_for<0, 2>([&](auto Mb) {
+    constexpr int mb = decltype(Mb)::value;
+    Moments m{};
+    static_for<0, M::NSHELL>([&](auto L) {
+      constexpr int l = decltype(L)::value;
+      ShellSums a{};
+      static_for<shell_pair_begin<M>(l), shell_pair_begin<M>(l + 1)>([&](auto K) {
+        constexpr int k = decltype(K)::value;
+        const double v = static_cast<double>(f[2 * k + mb]);
+        a.template add_pair<M, k>(v, v);
+        a.pin();
+      });
+      a.template fold<M, l>(m);
+    });
+    // finish this half first (an empty statement; without it the compiler
+    // keeps both halves' sums live and spills 61 registers)
+    asm volatile("" : "+v"(m.N0), "+v"(m.Nx), "+v"(m.Ny), "+v"(m.Nz), "+v"(m.T00), "+v"(m.T0x), "+v"(m.T0y), "+v"(m.T0z),
+                 "+v"(m.Txx), "+v"(m.Tyy), "+v"(m.Tzz), "+v"(m.Txy), "+v"(m.Txz), "+v"(m.Tyz));
+    h[mb] = m;
+  });
+  const Moments &p = h[0], &q = h[1];
+  return Moments{p.N0 + q.N0,   p.Nx - q.Nx,   p.Ny - q.Ny,   p.Nz - q.Nz,   p.T00 + q.T00, p.T0x - q.T0x, p.T0y - q.T0y,
+                 p.T0z - q.T0z, p.Txx + q.Txx, p.Tyy + q.Tyy, p.Tzz + q.Tzz, p.Txy + q.Txy, p.Txz + q.Txz, p.Tyz + q.Tyz};
+}
+
+// Byte offset of population 0 of cell c in a buffer below 4 GiB:
+// tile_elem(c) * sizeof(S), from c + (c / TILE) (Q - 1) TILE.
+template <class M, class S>
+__device__ __forceinline__ uint32_t tile_bytes32(int c) {
+  constexpr uint32_t T = TILE<S>, B = static_cast<uint32_t>(sizeof(S));
+  const uint32_t u = static_cast<uint32_t>(c);
+  return (u / T) * ((M::Q - 1) * T * B) + u * B;
+}
+template <class M, class S>
+constexpr bool tile_bytes32_fit(int64_t cells) {
+  return (cells + TILE<S> - 1) / TILE<S> * TILE<S> * M::Q * static_cast<int64_t>(sizeof(S)) <= (int64_t(1) << 32);
+}
+
+template <class M, bool WALLS>
+__global__ void __launch_bounds__(step_block<PULL>) __attribute__((amdgpu_waves_per_eu(2)))
+k_step_any(const float *__restrict__ cur, float *__restrict__ nxt, Geom g, Relax rx, unsigned *__restrict__ status,
+           const uint8_t *__restrict__ solid) {
+  using S = float;
+  constexpr int T = TILE<S>;
+  const int cell = pair_block_order(blockIdx.x, gridDim.x) * step_block<PULL> + static_cast<int>(threadIdx.x);
+  if (cell >= g.cells) return;
+  if constexpr (WALLS) {
+    if (solid[cell]) return;
+  }
+  int x, y, z;
+  cell_coords(cell, g, x, y, z);
+  const Shifts sh(x, y, z, g);
+  S f[M::Q];
+  static_for<0, M::Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    constexpr Point P = M::P[i];
+    const uint32_t off = tile_bytes32<M, S>(sh.template back<P.tx, P.ty, P.tz>());
+    f[i] = *reinterpret_cast<const S *>(reinterpret_cast<const char *>(cur + i * T) + off);
+  });
+  __builtin_amdgcn_sched_barrier(0);
+  const Moments m = moments_by_member<M>(f);
+  __builtin_amdgcn_sched_barrier(0);
+  Frame fr;
+  const unsigned flags = landau_frame(m, fr);
+  const double tau = relaxation_time<M>(rx, fr.n, fr.T);
+  __builtin_amdgcn_sched_barrier(0);
+  const EqCoef<M> e = eq_coefficients<M>(fr.n, fr.T, fr.U0, fr.Ux, fr.Uy, fr.Uz);
+  const double gd = fr.U0 / tau, gs = gd * M::INV_R;
+  const S gg = S(gd), bx = S(gs * fr.vx), by = S(gs * fr.vy), bz = S(gs * fr.vz);
+  char *own = reinterpret_cast<char *>(nxt);
+  const uint32_t o = tile_bytes32<M, S>(cell);
+  static_for<0, M::NSHELL>([&](auto L) {
+    constexpr int l = decltype(L)::value;
+    const ShellCoef<M, S> s = shell_coefficients<M, l, S>(e);
+    static_for<shell_pair_begin<M>(l), shell_pair_begin<M>(l + 1)>([&](auto K) {
+      constexpr int k = decltype(K)::value;
+      constexpr Point P = M::P[2 * k];
+      S E, O;
+      shell_eval<M, 2 * k, S>(s, E, O);
+      S t = S(0);
+      if constexpr (P.tx != 0) t = fmadd(S(P.tx), bx, t);
+      if constexpr (P.ty != 0) t = fmadd(S(P.ty), by, t);
+      if constexpr (P.tz != 0) t = fmadd(S(P.tz), bz, t);
+      const S a = f[2 * k], b = f[2 * k + 1];
+      const S ea = S(P.w) * (E + O), eb = S(P.w) * (E - O);
+      __builtin_nontemporal_store(fmadd(gg - t, ea - a, a),
+                                  reinterpret_cast<S *>(own + (2 * k) * T * sizeof(S) + o));
+      __builtin_nontemporal_store(fmadd(gg + t, eb - b, b),
+                                  reinterpret_cast<S *>(own + (2 * k + 1) * T * sizeof(S) + o));
+    });
+  });
+  if (flags) atomicOr(status, flags);
+}
+
 // Initial state: local equilibrium of (n, eps, v) in every cell, stored so
 // that the next gather returns it (scatter to x - theta_i).
 // With aa != 0 the state is written in the natural AA layout (slot (i, x) =
