@@ -889,6 +889,22 @@ __global__ void __launch_bounds__(BLOCK) k_init(const double *__restrict__ n_, c
   if (flags) atomicOr(status, flags);
 }
 
+// Sets *bad if a cell of the fields n, eps, vx, vy, vz (`cells` values each, one
+// after the other) is not finite or has n <= 0, eps <= 0 or |v| >= 1 (v2 < 1
+// holds for no NaN or infinity).
+__global__ void __launch_bounds__(BLOCK) k_check(const double *__restrict__ a, int64_t cells,
+                                                 unsigned *__restrict__ bad) {
+  bool ok = true;
+  for (int64_t c = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; c < cells;
+       c += static_cast<int64_t>(gridDim.x) * BLOCK) {
+    const double n = a[c], eps = a[cells + c];
+    const double vx = a[2 * cells + c], vy = a[3 * cells + c], vz = a[4 * cells + c];
+    const double v2 = vx * vx + vy * vy + vz * vz;
+    ok = ok && n > 0.0 && eps > 0.0 && __builtin_isfinite(n) && __builtin_isfinite(eps) && v2 < 1.0;
+  }
+  if (!ok) *bad = 1u;
+}
+
 // Macroscopic fields of the current pre-collision state (zero at solid
 // cells when `solid` is given).
 template <class M, class S>
