@@ -161,6 +161,18 @@ bool any_kernel_fits(int64_t cells) {
   return cells >= (M::ORDER == 3 ? 196608 : 98304) && rlb::tile_bytes32_fit<M, float>(cells);
 }
 
+// float64 boxes of at most this many cells are stepped by k_step_split, the
+// rest by the two-lane kernel.  Walls and both streaming patterns follow one
+// rule, so that the patterns keep giving the same bits; the line is where the
+// in-place pattern stops gaining (us per step, two-lane / split, two buffers
+// and in place; third order: 16^3 12.1 / 9.8 and 14.0 / 9.5, 32^3 18.8 / 14.4 and
+// 17.3 / 15.8, 34x35x34 24.8 / 21.7 and 24.1 / 26.3, 64^3 124 / 114 and 110 / 111,
+// 101^3 389 / 440; second order: 16^3 7.3 / 6.9 and 7.6 / 6.4, 24^3 7.6 / 7.5 and
+// 10.0 / 7.6, 32^3 9.8 / 9.5 and 10.1 / 10.5).
+template <class M>
+constexpr int64_t split_kernel_cells = M::ORDER == 3 ? 36864 : 16384;
+static_assert(rlb::tile_bytes32_fit<rlb::M3, double>(split_kernel_cells<rlb::M3>));
+
 // The step kernels of one box, with or without walls, for access AC (with
 // AA the input and output buffer is the same).
 template <class M, bool WALLS, int AC>
@@ -168,7 +180,13 @@ void launch_step_kernels(rlb_solver *s, const rlb::Geom &g, const rlb::Relax &r)
   const uint8_t *solid = WALLS ? s->d_solid : nullptr;
   void *in = s->buf[s->cur];
   void *out = AC == rlb::PULL ? s->buf[1 - s->cur] : s->buf[s->cur];
-  if (s->cfg.precision == RLB_FP64) {
+  // the split kernel has one form of the odd AA step
+  constexpr int SAC = AC == rlb::AA_ODD_WIDE ? rlb::AA_ODD : AC;
+  if (s->cfg.precision == RLB_FP64 && s->cells <= split_kernel_cells<M>) {
+    const dim3 grid(static_cast<unsigned>((s->cells + 63) / 64)), block(64 * M::NSHELL);
+    rlb::k_step_split<M, WALLS, SAC><<<grid, block, 0, s->stream>>>(
+        static_cast<const double *>(in), static_cast<double *>(out), g, r, s->status, solid);
+  } else if (s->cfg.precision == RLB_FP64) {
     constexpr int TB = rlb::pair_block<M, double, AC>;
     const dim3 grid(static_cast<unsigned>((s->cells + TB / 2 - 1) / (TB / 2))), block(TB);
     rlb::k_step<M, double, WALLS, AC><<<grid, block, 0, s->stream>>>(

@@ -782,7 +782,7 @@ template <class M, class S>
 __device__ __forceinline__ uint32_t tile_bytes32(int c) {
   constexpr uint32_t T = TILE<S>, B = static_cast<uint32_t>(sizeof(S));
   const uint32_t u = static_cast<uint32_t>(c);
-  return (u / T) * ((M::Q - 1) * T * B) + u * B;
+  return __umul24(u / T, (M::Q - 1) * T * B) + u * B; // both below 2^24
 }
 template <class M, class S>
 constexpr bool tile_bytes32_fit(int64_t cells) {

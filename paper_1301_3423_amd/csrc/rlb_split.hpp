@@ -1,5 +1,5 @@
 // The time step with the populations of a cell split over the wavefronts of
-// a workgroup, for tubes.  A lane that holds a whole cell (or half of one)
+// a workgroup, for tubes and small boxes.  A lane that holds a whole cell (or half of one)
 // issues over 4000 instructions per step: 8-10 us at one wavefront per SIMD,
 // however few cells there are.  Here the chain is cut:
 //
@@ -218,6 +218,79 @@ __device__ __forceinline__ void for_group(int grp, F &&f) {
   } else {
     f(std::integral_constant<int, G>{});
   }
+}
+
+// ---- one float64 step of a small box ------------------------------------------
+//
+// While the chip is not full a step lasts as long as a workgroup: the launch
+// (3.8 us), the gathers' latency and one wavefront's chain, 1500 vector
+// instructions here against 4300 in the two-lane kernel (k_step), which a
+// larger box keeps hidden behind its memory traffic.  1 x 1 x 1600 10.7 -> 8.1
+// us per step, 16^3 12.1 -> 9.8, 32^3 18.8 -> 14.4 (4.7 TB/s, from the caches).
+// Offsets are 32-bit; the 24-bit multiply that forms them matters (32^3 16.5
+// us with a 32-bit one).
+template <class M, bool WALLS, int AC>
+__global__ void __launch_bounds__(64 * M::NSHELL) __attribute__((amdgpu_waves_per_eu(2)))
+k_step_split(InPtr<double, AC> cur, OutPtr<double, AC> nxt, Geom g, Relax rx, unsigned *__restrict__ status,
+             const uint8_t *__restrict__ solid) {
+  using S = double;
+  constexpr int NG = M::NSHELL;
+  using D = Split<M, S, NG>;
+  constexpr int T = TILE<S>;
+  __shared__ double part[D::SHARES][D::SHARE][64];
+  __shared__ S coef[M::NSHELL][SpatialTable<M>::NS][64];
+  const int grp = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  int cell = pair_block_order(blockIdx.x, gridDim.x) * 64 + lane;
+  bool active = cell < g.cells;
+  if (!active) cell = g.cells - 1; // computed, never stored
+  if constexpr (WALLS) active = active && solid[cell] == 0;
+  int x, y, z;
+  cell_coords(cell, g, x, y, z);
+  const Shifts sh(x, y, z, g);
+  const uint32_t own = tile_bytes32<M, S>(cell);
+  const char *in = reinterpret_cast<const char *>(cur);
+  char *out = reinterpret_cast<char *>(nxt);
+  constexpr int SEG = T * static_cast<int>(sizeof(S)); // bytes from a population to the next
+  typename D::Pops f;
+  for_group<NG>(grp, [&](auto G) {
+    constexpr int q = decltype(G)::value;
+    D::template points<q>([&](auto I, auto P) {
+      constexpr int i = decltype(I)::value, p = decltype(P)::value;
+      constexpr Point PT = M::P[i];
+      const uint32_t o = AC == AA_EVEN ? own : tile_bytes32<M, S>(sh.template back<PT.tx, PT.ty, PT.tz>());
+      f[p] = *reinterpret_cast<const S *>(in + (aa_odd(AC) ? i ^ 1 : i) * SEG + o);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    share_sums<D, M, q>(f, part, lane);
+  });
+  __syncthreads();
+  const Moments m = gathered_moments<D, M>(part, lane);
+  Frame fr;
+  const unsigned flags = landau_frame(m, fr);
+  const double tau = relaxation_time<M>(rx, fr.n, fr.T);
+  const MJ mj = mj_of(fr.n, fr.T, fr.U0, fr.Ux, fr.Uy, fr.Uz);
+  for_group<NG>(grp, [&](auto G) { share_coefficients<M, S, NG, decltype(G)::value>(mj, coef, lane); });
+  __syncthreads();
+  for_group<NG>(grp, [&](auto G) {
+    constexpr int q = decltype(G)::value;
+    relax_group<D, M, S, q>(f, coef, lane, fr, tau);
+    // AA_ODD: the offsets are formed again rather than kept through the
+    // arithmetic (keeping them spills 112 registers: 64^3 119 instead of 111 us)
+    int xs = x;
+    asm volatile("" : "+v"(xs));
+    const Shifts to(xs, y, z, g);
+    if (active)
+      D::template points<q>([&](auto I, auto P) {
+        constexpr int i = decltype(I)::value, p = decltype(P)::value;
+        constexpr Point PT = M::P[i];
+        if constexpr (aa_odd(AC))
+          *reinterpret_cast<S *>(out + i * SEG + tile_bytes32<M, S>(to.template fwd<PT.tx, PT.ty, PT.tz>())) = f[p];
+        else
+          __builtin_nontemporal_store(f[p], reinterpret_cast<S *>(out + (AC == AA_EVEN ? i ^ 1 : i) * SEG + own));
+      });
+  });
+  if (active && flags && grp == 0) atomicOr(status, flags);
 }
 
 // ---- several steps of many tubes in one launch -------------------------------
