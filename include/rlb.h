@@ -319,9 +319,10 @@ void rlb_batch_destroy(rlb_batch *b);
  * chunk_steps launches; the last issue may end with fewer; a long tube run
  * as a box by chunk_steps * max(1, 262144 / nz)), or each of its
  * tubes by max(chunk_steps, chunk_steps * 8192 / nz) steps, all resident
- * tubes of one precision and model together, as in a batch.  Mixed-precision
- * tubes of 2048 cells or more run as 1 x 1 x nz boxes (box kernels), on the
- * tube stream of their precision.
+ * tubes of one precision and model in one persistent launch.  Tubes of 2048
+ * cells or more run as 1 x 1 x nz boxes (box kernels, which spread a step
+ * over many CUs, where a persistent tube launch gives a tube one CU), on
+ * the tube stream of their precision.
  * The four streams should each have a hardware queue: a process that has
  * other busy streams should raise GPU_MAX_HW_QUEUES (HIP's default is 4).
  * A request's result does not depend on what else is resident (the kernels

@@ -882,7 +882,10 @@ bool valid_tube(const rlb_tube &tb) {
 
 // Chunks of one wavefront in k_tubes, and the most (step, chunk) items one
 // launch gives a tube.
-int64_t tube_chunks(int32_t n) { return (static_cast<int64_t>(n) + rlb::TUBE_CHUNK - 1) / rlb::TUBE_CHUNK; }
+int64_t tube_chunks(int32_t n, int precision) {
+  const int ch = precision == RLB_FP64 ? rlb::TUBE_CHUNK<double> : rlb::TUBE_CHUNK<float>;
+  return (static_cast<int64_t>(n) + ch - 1) / ch;
+}
 constexpr int64_t TUBE_ITEMS_MAX = (int64_t(1) << 31) - 1;
 
 size_t batch_header_bytes(int ntubes) {
@@ -1232,7 +1235,7 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
   for (int j = 0; j < b->ntubes; ++j) {
     if (steps[j] == 0) continue;
     jobs.push_back({b->desc[j], j, steps[j]});
-    flow = flow && tube_chunks(b->tubes[j].n) <= rlb::TUBE_FLOW_CHUNKS;
+    flow = flow && tube_chunks(b->tubes[j].n, b->precision) <= rlb::TUBE_FLOW_CHUNKS<float>;
   }
   // tests of the stall path bound the waits of k_tubes to a few polls; where
   // that is asked for, the batch takes the kernel that waits
@@ -1262,7 +1265,7 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     std::vector<int> flow;
     for (int j = 0; j < b->ntubes; ++j) {
       if (rem[j] == 0) continue;
-      now[j] = std::min<int64_t>(rem[j], TUBE_ITEMS_MAX / tube_chunks(b->tubes[j].n));
+      now[j] = std::min<int64_t>(rem[j], TUBE_ITEMS_MAX / tube_chunks(b->tubes[j].n, b->precision));
       flow.push_back(j);
     }
     if (flow.empty()) break;
@@ -1282,8 +1285,8 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     RLB_HIP(hipMemcpyAsync(b->d_order, b->h_order, k * sizeof(int), hipMemcpyHostToDevice, b->stream));
     RLB_HIP(hipEventRecord(b->staged, b->stream));
     b->staged_pending = true;
-    rlb::k_tubes<<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(reinterpret_cast<float *>(b->pops), b->d_desc,
-                                                                   b->d_order, b->d_status);
+    rlb::k_tubes<rlb::M3, float><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, b->stream>>>(
+        reinterpret_cast<float *>(b->pops), b->d_desc, b->d_order, b->d_status);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_tubes launch");
     for (int j = 0; j < b->ntubes; ++j) {
@@ -1469,16 +1472,17 @@ int64_t request_cells(const rlb_request &r) {
   return static_cast<int64_t>(r.nx) * r.ny * r.nz;
 }
 
-// Mixed-precision tubes of at least this many cells run as 1 x 1 x n boxes
-// (still on the tube stream of their precision); their results are those of
-// the box kernels' rounding.
+// Tubes of at least this many cells run as 1 x 1 x n boxes (still on the
+// tube stream of their precision): the box kernels spread a step over n / 64
+// workgroups (many CUs), where the persistent tube launch gives each tube one
+// CU (about 8 MLUPS in float64, so a tube of 8000 cells and 2000 steps would
+// take 2 s).
 constexpr int32_t TUBE_AS_BOX_CELLS = 2048;
 
-bool runs_as_box(const rlb_request &r) {
-  return r.kind == RLB_REQ_BOX || (r.precision == RLB_MIXED && r.nz >= TUBE_AS_BOX_CELLS);
-}
-// the server's mixed tubes always fit the flags of k_tubes
-static_assert(TUBE_AS_BOX_CELLS / rlb::TUBE_CHUNK <= rlb::TUBE_FLOW_CHUNKS);
+bool runs_as_box(const rlb_request &r) { return r.kind == RLB_REQ_BOX || r.nz >= TUBE_AS_BOX_CELLS; }
+// the server's tubes always fit the dataflow form of the tube kernel
+static_assert(TUBE_AS_BOX_CELLS / rlb::TUBE_CHUNK<double> <= rlb::TUBE_FLOW_CHUNKS<double> &&
+              TUBE_AS_BOX_CELLS / rlb::TUBE_CHUNK<float> <= rlb::TUBE_FLOW_CHUNKS<float>);
 
 bool request_valid(const rlb_request &r, std::string &why) {
   if (r.kind != RLB_REQ_TUBE && r.kind != RLB_REQ_BOX) return why = "bad kind", false;
@@ -1714,13 +1718,17 @@ constexpr int64_t TUBE_ROUND_CELLS = 8192;
 
 int64_t tube_round_steps(const rlb_server *sv, const ServeReq *q) {
   const int64_t budget = static_cast<int64_t>(sv->chunk) * TUBE_ROUND_CELLS / std::max<int64_t>(q->r.nz, 1);
-  // k_tubes counts a launch's (step, chunk) items in 32 bits
-  const int64_t cap = TUBE_ITEMS_MAX / tube_chunks(q->r.nz);
+  // the tube kernel counts a launch's (step, chunk) items in 32 bits
+  const int64_t cap = TUBE_ITEMS_MAX / tube_chunks(q->r.nz, q->r.precision);
   return std::min<int64_t>(std::min<int64_t>(q->remaining, cap), std::max<int64_t>(sv->chunk, budget));
 }
 
+// (Launches of k_tubes_tile shorten a burst of few requests, 305 to 196 ms for
+// 24, but under a stream of arrivals each of a tube's hundred launches waits
+// for the boxes' workgroups to leave: p99 of the tubes 3.3 s instead of 0.5 s.
+// A workgroup that is resident keeps its place.)
 int tubes_advance(rlb_server *sv, int prec, int order, bool &issued) {
-  // all resident tubes of this precision and model together
+  // all resident tubes of this precision and model, one persistent launch
   std::vector<ServeReq *> tubes;
   for (ServeReq *q : sv->resident)
     if (!runs_as_box(q->r) && q->r.precision == prec && norm_order(q->r.order) == order && q->remaining > 0)
@@ -1732,49 +1740,38 @@ int tubes_advance(rlb_server *sv, int prec, int order, bool &issued) {
     return static_cast<double>(a->r.nz) * tube_round_steps(sv, a) >
            static_cast<double>(b->r.nz) * tube_round_steps(sv, b);
   });
-  std::vector<TubeJob> jobs;
+  int k = 0;
   for (ServeReq *q : tubes) {
-    TubeJob job;
-    job.d.off[0] = q->tube_off[0];
-    job.d.off[1] = q->tube_off[1];
-    job.d.n = q->r.nz;
-    job.d.cur = q->cur;
-    job.d.mode = q->r.tau_mode == RLB_TAU_ETA_S ? 1 : 0;
-    job.d.spin_limit = 0;
-    job.d.tau = q->r.tau;
-    job.d.eta_s = q->r.eta_s;
-    job.status = q->slot;
-    job.steps = tube_round_steps(sv, q);
-    job.d.steps = job.steps;
-    jobs.push_back(job);
+    rlb::TubeDesc &d = sv->h_desc[p][q->slot];
+    d.off[0] = q->tube_off[0];
+    d.off[1] = q->tube_off[1];
+    d.steps = tube_round_steps(sv, q);
+    d.n = q->r.nz;
+    d.cur = q->cur;
+    d.mode = q->r.tau_mode == RLB_TAU_ETA_S ? 1 : 0;
+    d.spin_limit = 0;
+    d.tau = q->r.tau;
+    d.eta_s = q->r.eta_s;
+    sv->h_order[p][k++] = q->slot;
   }
   hipStream_t st = sv->streams[tube_stream(p)];
-  // float64 and the second-order model always go by tiles, so that a result
-  // does not depend on what else is resident; third-order float32 has the
-  // same bits either way
-  const TilePlan plan = plan_tiles(jobs, prec, order);
-  int64_t per_launch = 1; // steps after which a tube's buffers change places
-  if (prec == RLB_MIXED && order == RLB_ORDER3 && flow_is_faster(jobs, plan)) {
-    int k = 0;
-    for (const TubeJob &job : jobs) {
-      sv->h_desc[p][job.status] = job.d;
-      sv->h_order[p][k++] = job.status;
-    }
-    RLB_HIP(hipMemcpyAsync(sv->d_desc[p], sv->h_desc[p], sv->max_tubes * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
-    RLB_HIP(hipMemcpyAsync(sv->d_order[p], sv->h_order[p], k * sizeof(int), hipMemcpyHostToDevice, st));
-    rlb::k_tubes<<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, st>>>(reinterpret_cast<float *>(sv->pool), sv->d_desc[p],
-                                                            sv->d_order[p], sv->d_status);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "serve k_tubes");
-  } else {
-    const int rc = run_tiles(jobs, plan, prec, order, sv->pool, sv->h_desc[p], sv->h_order[p], sv->d_desc[p],
-                             sv->d_order[p], sv->d_status, st, nullptr);
-    if (rc != RLB_OK) return rc;
-    per_launch = plan.ksteps;
-  }
+  RLB_HIP(hipMemcpyAsync(sv->d_desc[p], sv->h_desc[p], sv->max_tubes * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
+  RLB_HIP(hipMemcpyAsync(sv->d_order[p], sv->h_order[p], k * sizeof(int), hipMemcpyHostToDevice, st));
+  with_model(order, [&](auto m) {
+    using M = decltype(m);
+    if (prec == RLB_FP64)
+      rlb::k_tubes<M, double><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, st>>>(reinterpret_cast<double *>(sv->pool),
+                                                                          sv->d_desc[p], sv->d_order[p], sv->d_status);
+    else
+      rlb::k_tubes<M, float><<<dim3(k), dim3(rlb::TUBE_BLOCK), 0, st>>>(reinterpret_cast<float *>(sv->pool),
+                                                                         sv->d_desc[p], sv->d_order[p], sv->d_status);
+    return 0;
+  });
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, "serve k_tubes");
   for (ServeReq *q : tubes) {
     const int64_t s = tube_round_steps(sv, q);
-    q->cur ^= static_cast<int>(((s + per_launch - 1) / per_launch) & 1);
+    q->cur ^= static_cast<int>(s & 1);
     q->remaining -= s;
   }
   return RLB_OK;

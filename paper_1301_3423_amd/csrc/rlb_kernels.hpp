@@ -427,8 +427,8 @@ struct TubeDesc {
 
 inline constexpr int TUBE_BLOCK = 512; // one workgroup fills a CU at two waves per SIMD
 
-// Inside a workgroup the tube is cut into chunks of one wavefront (64 cells,
-// one per lane), and the
+// Inside a workgroup the tube is cut into chunks of one wavefront (64 cells
+// in float32, one per lane; 32 in float64, two lanes per cell), and the
 // work is the sequence of (step s, chunk c) in the order k = s * nch + c.
 // Each wavefront takes the next k from a counter in LDS, waits until the
 // chunks its gathers reach (c - 1, c and c + 1 in the interior -- a gather
@@ -442,11 +442,14 @@ inline constexpr int TUBE_BLOCK = 512; // one workgroup fills a CU at two waves 
 // nearly the same time, so the cache lines they share are fetched once.
 // Every dependence of k is on smaller k, all of which were taken earlier,
 // so the work always progresses.  A step count per chunk is kept modulo
-// 256 (chunks in progress are at most a few steps apart).  Third-order
-// float32 only, for many tubes; everything else takes k_tubes_tile.
-inline constexpr int TUBE_CHUNK = 64;
-// LDS flag bytes
-inline constexpr int TUBE_FLOW_CHUNKS = 65536;
+// 256 (chunks in progress are at most a few steps apart).  The server's tubes
+// take this kernel, and large third-order float32 batches; other batches take
+// k_tubes_tile.
+template <class S>
+inline constexpr int TUBE_CHUNK = sizeof(S) == 8 ? 32 : 64;
+// LDS flag bytes: float64 keeps 128 KB for its stash, float32 has no stash
+template <class S>
+inline constexpr int TUBE_FLOW_CHUNKS = sizeof(S) == 8 ? 24576 : 65536;
 // polls of a wait before it gives up and flags the tube (about 0.2 s; a
 // normal wait is a few microseconds); bounds every wait
 inline constexpr int TUBE_SPIN_LIMIT = 1 << 22;
@@ -517,16 +520,17 @@ __device__ __forceinline__ void tube_cell_step(const S *__restrict__ in, S *__re
 }
 
 // The tube's work in (step, chunk) order; `order` lists the workgroups'
-// tubes, each with at most TUBE_FLOW_CHUNKS chunks and fewer than 2^31
+// tubes, each with at most TUBE_FLOW_CHUNKS<S> chunks and fewer than 2^31
 // (step, chunk) items in this launch (the host splits longer runs).
+template <class M, class S>
 __global__ void __launch_bounds__(TUBE_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
-k_tubes(float *__restrict__ base, const TubeDesc *__restrict__ desc, const int *__restrict__ order,
+k_tubes(S *__restrict__ base, const TubeDesc *__restrict__ desc, const int *__restrict__ order,
         unsigned *__restrict__ status) {
-  using M = M3;
-  using S = float;
+  constexpr bool f64 = sizeof(S) == 8;
   constexpr int TB = TUBE_BLOCK;
-  constexpr int CH = TUBE_CHUNK;
-  __shared__ uint8_t done_[TUBE_FLOW_CHUNKS];
+  constexpr int CH = TUBE_CHUNK<S>;
+  __shared__ S lds[stash_rows<M, S>][f64 ? TB : 1];
+  __shared__ uint8_t done_[TUBE_FLOW_CHUNKS<S>];
   __shared__ unsigned next_;
   const int j = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
   const TubeDesc d = desc[j]; // uniform: scalar loads
@@ -540,6 +544,9 @@ k_tubes(float *__restrict__ base, const TubeDesc *__restrict__ desc, const int *
   rx.tau = d.tau;
   rx.eta_s = d.eta_s;
   const int lane = static_cast<int>(threadIdx.x) & 63;
+  // float64: cell (lane & 31) of the wavefront's 32 on two lanes; float32:
+  // one cell per lane
+  const int slot = f64 ? (lane & 31) : lane;
   unsigned flags = 0;
   const unsigned nch = static_cast<unsigned>((d.n + CH - 1) / CH);
   volatile uint8_t *done = done_;
@@ -575,7 +582,10 @@ k_tubes(float *__restrict__ base, const TubeDesc *__restrict__ desc, const int *
     const int cur = (d.cur + static_cast<int>(st & 1u)) & 1;
     const S *in = base + (cur ? d.off[1] : d.off[0]);
     S *out = base + (cur ? d.off[0] : d.off[1]);
-    tube_cell_step<M, S>(in, out, g, rx, static_cast<int>(c) * CH + lane, flags);
+    if constexpr (f64)
+      pair_cell_step<M, S, TB>(in, out, g, rx, static_cast<int>(c) * CH + slot, lds, flags);
+    else
+      tube_cell_step<M, S>(in, out, g, rx, static_cast<int>(c) * CH + slot, flags);
     // this chunk's stores complete before it is marked done
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) done[c] = static_cast<uint8_t>(st + 1);
