@@ -119,6 +119,7 @@ struct rlb_solver {
   const rlb::Link *d_links = nullptr;
   int64_t nlinks = 0;
   uint64_t solid_hash = 0; // FNV-1a of the mask, 0 without walls
+  bool alone = true;       // false for the server's boxes: other streams keep the chip full
 };
 
 namespace {
@@ -168,7 +169,10 @@ bool any_kernel_fits(int64_t cells) {
 // and in place; third order: 16^3 12.1 / 9.8 and 14.0 / 9.5, 32^3 18.8 / 14.4 and
 // 17.3 / 15.8, 34x35x34 24.8 / 21.7 and 24.1 / 26.3, 64^3 124 / 114 and 110 / 111,
 // 101^3 389 / 440; second order: 16^3 7.3 / 6.9 and 7.6 / 6.4, 24^3 7.6 / 7.5 and
-// 10.0 / 7.6, 32^3 9.8 / 9.5 and 10.1 / 10.5).
+// 10.0 / 7.6, 32^3 9.8 / 9.5 and 10.1 / 10.5).  Not for the server's boxes: beside
+// a large box its workgroups (four wavefronts, 60 KB of LDS) find no place, as
+// that box's smaller ones take whatever is freed, and small requests wait
+// until it ends (served tubes' p99 7.7 s with it, 0.5 s without).
 template <class M>
 constexpr int64_t split_kernel_cells = M::ORDER == 3 ? 36864 : 16384;
 static_assert(rlb::tile_bytes32_fit<rlb::M3, double>(split_kernel_cells<rlb::M3>));
@@ -182,7 +186,7 @@ void launch_step_kernels(rlb_solver *s, const rlb::Geom &g, const rlb::Relax &r)
   void *out = AC == rlb::PULL ? s->buf[1 - s->cur] : s->buf[s->cur];
   // the split kernel has one form of the odd AA step
   constexpr int SAC = AC == rlb::AA_ODD_WIDE ? rlb::AA_ODD : AC;
-  if (s->cfg.precision == RLB_FP64 && s->cells <= split_kernel_cells<M>) {
+  if (s->cfg.precision == RLB_FP64 && s->alone && s->cells <= split_kernel_cells<M>) {
     const dim3 grid(static_cast<unsigned>((s->cells + 63) / 64)), block(64 * M::NSHELL);
     rlb::k_step_split<M, WALLS, SAC><<<grid, block, 0, s->stream>>>(
         static_cast<const double *>(in), static_cast<double *>(out), g, r, s->status, solid);
@@ -1578,6 +1582,7 @@ int admit(rlb_server *sv, ServeReq *q) {
     rlb_config cfg{r.nx, r.ny, r.nz, r.precision, r.tau_mode, r.tau, r.eta_s, r.order, RLB_PATTERN_AB};
     int rc = rlb_create(&q->box, &cfg, sv->pool + q->off, q->bytes, sv->streams[q->stream_idx]);
     if (rc != RLB_OK) return rc;
+    q->box->alone = false;
     return rlb_init_fields(q->box, f, f + C, f + 2 * C, f + 3 * C, f + 4 * C, 0);
   }
   // tube: two buffers at q->off, staging through the second one
@@ -1723,10 +1728,9 @@ int64_t tube_round_steps(const rlb_server *sv, const ServeReq *q) {
   return std::min<int64_t>(std::min<int64_t>(q->remaining, cap), std::max<int64_t>(sv->chunk, budget));
 }
 
-// (Launches of k_tubes_tile shorten a burst of few requests, 305 to 196 ms for
-// 24, but under a stream of arrivals each of a tube's hundred launches waits
-// for the boxes' workgroups to leave: p99 of the tubes 3.3 s instead of 0.5 s.
-// A workgroup that is resident keeps its place.)
+// (k_tubes_tile shortens a burst of few requests, 305 to 196 ms for 24, but
+// its launches find no place beside a large box, as k_step_split's; a
+// workgroup that is resident keeps its place.)
 int tubes_advance(rlb_server *sv, int prec, int order, bool &issued) {
   // all resident tubes of this precision and model, one persistent launch
   std::vector<ServeReq *> tubes;
