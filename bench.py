@@ -324,7 +324,7 @@ def summarize_profiles(prof_root):
     from paper_1301_3423_amd import inputs
     cells = sum(t["N"] for t in inputs.tube_batch(512, 4))
     # float64 batches run as many launches of k_tubes_tile: no one-launch summary
-    for prec, stem, kern in (("mixed", "k_tubes_f32_512tubes", "k_tubes"),):
+    for prec, stem, kern in (("mixed", "k_tubes_f32_512tubes", "k_tubes<Model<3>, float>"),):
         if kern not in times or kern not in fetch or kern not in write:
             continue
         # the bench launches 2 warm-up steps, then the 500 timed ones: the longest dispatch
@@ -862,7 +862,7 @@ def main():
             r = run_tubes(prec)
             tube_runs[prec] = r
             print("bench: tubes %s %.1f MLUPS" % (prec, r["mlups"]), file=sys.stderr, flush=True)
-            kv = (profile_fields("k_tubes") if prec == "mixed" else None) or {}
+            kv = (profile_fields("k_tubes<Model<3>, float>") if prec == "mixed" else None) or {}
             tubes[prec] = {"value": round(r["mlups"], 2), "unit": "MLUPS", "launch_ms": round(r["ms"], 3),
                            "achieved_GBps": round(r["achieved_gbs"], 1), "cells": r["cells"],
                            "tubes_flagged": r["tubes_flagged"],

@@ -1000,7 +1000,7 @@ TilePlan plan_tiles(const std::vector<TubeJob> &jobs, int precision, int order) 
   return best;
 }
 
-// Whether the one-workgroup-per-tube kernel takes less time.  It exists for
+// Whether the one-workgroup-per-tube kernel takes less time.  Batches use it for
 // third-order float32, whose results are the same bits either way: with some
 // 300 tubes or more it keeps every CU at work and computes no cell twice
 // (512 tubes of 200-4000 cells: 217 us per step against 233 by tiles; 96 of
