@@ -254,7 +254,7 @@ int rlb_set_walls(rlb_solver *s, const uint8_t *solid, void *d_buf, size_t bytes
  * 1 x 1 x n lattice on which only the z displacement of each point moves
  * anything.  A batch holds many tubes of one precision in one caller-owned
  * buffer and advances all of them together: launches of up to five steps
- * spread the cells over the chip, 64 lanes to a workgroup.  Many third-order
+ * (float64: three) spread the cells over the chip, 64 (32) to a workgroup.  Many third-order
  * mixed-precision tubes (some 300 or more; same results) take one persistent
  * launch instead: one workgroup per tube, launched longest-work-first, whose
  * wavefronts take the tube's (step, chunk) work in order and wait only for

@@ -163,16 +163,12 @@ bool any_kernel_fits(int64_t cells) {
 }
 
 // float64 boxes of at most this many cells are stepped by k_step_split, the
-// rest by the two-lane kernel.  Walls and both streaming patterns follow one
-// rule, so that the patterns keep giving the same bits; the line is where the
-// in-place pattern stops gaining (us per step, two-lane / split, two buffers
-// and in place; third order: 16^3 12.1 / 9.8 and 14.0 / 9.5, 32^3 18.8 / 14.4 and
-// 17.3 / 15.8, 34x35x34 24.8 / 21.7 and 24.1 / 26.3, 64^3 124 / 114 and 110 / 111,
-// 101^3 389 / 440; second order: 16^3 7.3 / 6.9 and 7.6 / 6.4, 24^3 7.6 / 7.5 and
-// 10.0 / 7.6, 32^3 9.8 / 9.5 and 10.1 / 10.5).  Not for the server's boxes: beside
-// a large box its workgroups (four wavefronts, 60 KB of LDS) find no place, as
-// that box's smaller ones take whatever is freed, and small requests wait
-// until it ends (served tubes' p99 7.7 s with it, 0.5 s without).
+// rest by the two-lane kernel, whose bits are the same (us per step, two-lane / split,
+// two buffers and in place; third order: 16^3 11.6 / 9.0 and 13.9 / 9.7, 32^3 18.6 /
+// 15.6 and 17.2 / 16.9; second order: 16^3 7.1 / 6.2 and 7.4 / 6.0).  The server's
+// boxes keep the two-lane kernel: it needs half as many workgroups, which counts
+// where other streams keep the chip full (200 steps of 32^3 beside a 256^3 box:
+// 10.5 ms, split 11.5).
 template <class M>
 constexpr int64_t split_kernel_cells = M::ORDER == 3 ? 36864 : 16384;
 static_assert(rlb::tile_bytes32_fit<rlb::M3, double>(split_kernel_cells<rlb::M3>));
@@ -187,7 +183,7 @@ void launch_step_kernels(rlb_solver *s, const rlb::Geom &g, const rlb::Relax &r)
   // the split kernel has one form of the odd AA step
   constexpr int SAC = AC == rlb::AA_ODD_WIDE ? rlb::AA_ODD : AC;
   if (s->cfg.precision == RLB_FP64 && s->alone && s->cells <= split_kernel_cells<M>) {
-    const dim3 grid(static_cast<unsigned>((s->cells + 63) / 64)), block(64 * M::NSHELL);
+    const dim3 grid(static_cast<unsigned>((s->cells + 31) / 32)), block(128);
     rlb::k_step_split<M, WALLS, SAC><<<grid, block, 0, s->stream>>>(
         static_cast<const double *>(in), static_cast<double *>(out), g, r, s->status, solid);
   } else if (s->cfg.precision == RLB_FP64) {
@@ -953,21 +949,21 @@ struct TileCost {
     return launches * start + std::max(launches * k * step, tiles / 256 * (load + k * work));
   }
 };
-// The kernel's forms: cells split over NSHELL wavefronts (the shortest
-// chain), or, in float32 with its same bits, over two (third order) or one
-// (second order), which repeat less of the frame's arithmetic.
-struct TileForm {
-  bool wide;
-  TileCost cost;
-};
-std::vector<TileForm> tile_forms(int precision, int order) {
-  if (precision == RLB_FP64)
-    return {{false, order == RLB_ORDER2 ? TileCost{3.0, 3.4, 3.2, 1.7} : TileCost{3.5, 4.4, 5.4, 2.6}}};
-  if (order == RLB_ORDER2) return {{false, {2.8, 3.3, 2.0, 1.3}}, {true, {2.6, 3.9, 1.6, 0.75}}};
-  return {{false, {2.9, 4.1, 3.4, 2.4}}, {true, {3.2, 6.0, 3.3, 1.8}}};
+TileCost tile_cost(int precision, int order) {
+  if (precision == RLB_FP64) return order == RLB_ORDER2 ? TileCost{2.5, 3.0, 1.1, 0.5} : TileCost{3.0, 4.9, 2.2, 1.1};
+  return order == RLB_ORDER2 ? TileCost{2.4, 3.7, 1.4, 0.4} : TileCost{3.1, 4.9, 2.4, 1.0};
 }
 
-int64_t tube_tiles(int32_t n, int k) { return (n + rlb::tube_tile_cells(k) - 1) / rlb::tube_tile_cells(k); }
+int tile_cells(int precision, int k) {
+  return precision == RLB_FP64 ? rlb::tube_tile_cells<double>(k) : rlb::tube_tile_cells<float>(k);
+}
+int tile_max_ksteps(int precision) {
+  return precision == RLB_FP64 ? rlb::TUBE_MAX_KSTEPS<double> : rlb::TUBE_MAX_KSTEPS<float>;
+}
+int64_t tube_tiles(int32_t n, int precision, int k) {
+  const int cells = tile_cells(precision, k);
+  return (n + cells - 1) / cells;
+}
 
 // A tube to advance: its descriptor (off, n, cur, mode, tau, eta_s), where
 // its status word lies, and how many steps.
@@ -979,24 +975,23 @@ struct TubeJob {
 
 struct TilePlan {
   int ksteps;
-  bool wide;
   double time; // estimate, us
 };
 
-// The form and the steps per launch of least estimated time.
+// The steps per launch of least estimated time.
 TilePlan plan_tiles(const std::vector<TubeJob> &jobs, int precision, int order) {
-  TilePlan best{1, false, -1.0};
-  for (const TileForm &f : tile_forms(precision, order))
-    for (int k = 1; k <= rlb::TUBE_MAX_KSTEPS; ++k) {
-      double launches = 0.0, tiles = 0.0;
-      for (const TubeJob &j : jobs) {
-        const double l = static_cast<double>((j.steps + k - 1) / k);
-        launches = std::max(launches, l);
-        tiles += l * static_cast<double>(tube_tiles(j.d.n, k));
-      }
-      const double t = f.cost.launches(k, launches, tiles);
-      if (best.time < 0.0 || t < best.time) best = {k, f.wide, t};
+  TilePlan best{1, -1.0};
+  const TileCost cost = tile_cost(precision, order);
+  for (int k = 1; k <= tile_max_ksteps(precision); ++k) {
+    double launches = 0.0, tiles = 0.0;
+    for (const TubeJob &j : jobs) {
+      const double l = static_cast<double>((j.steps + k - 1) / k);
+      launches = std::max(launches, l);
+      tiles += l * static_cast<double>(tube_tiles(j.d.n, precision, k));
     }
+    const double t = cost.launches(k, launches, tiles);
+    if (best.time < 0.0 || t < best.time) best = {k, t};
+  }
   return best;
 }
 
@@ -1038,7 +1033,7 @@ int run_tiles(std::vector<TubeJob> &jobs, const TilePlan &plan, int precision, i
     h_desc[i].steps = jobs[i].steps;
     h_desc[i].spin_limit = jobs[i].status;
     h_first[i] = tiles;
-    tiles += static_cast<int>(tube_tiles(jobs[i].d.n, k));
+    tiles += static_cast<int>(tube_tiles(jobs[i].d.n, precision, k));
   }
   RLB_HIP(hipMemcpyAsync(d_desc, h_desc, nt * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
   RLB_HIP(hipMemcpyAsync(d_first, h_first, nt * sizeof(int), hipMemcpyHostToDevice, st));
@@ -1047,7 +1042,7 @@ int run_tiles(std::vector<TubeJob> &jobs, const TilePlan &plan, int precision, i
   for (int round = 0;; ++round) {
     while (live > 0 && jobs[live - 1].steps <= static_cast<int64_t>(round) * k) {
       --live;
-      tiles -= static_cast<int>(tube_tiles(jobs[live].d.n, k));
+      tiles -= static_cast<int>(tube_tiles(jobs[live].d.n, precision, k));
     }
     if (live == 0) break;
     with_model(order, [&](auto m) {
@@ -1056,11 +1051,9 @@ int run_tiles(std::vector<TubeJob> &jobs, const TilePlan &plan, int precision, i
         kernel(dim3(tiles), pops, d_desc, d_first, static_cast<int>(live), round, k, d_status, st);
       };
       if (precision == RLB_FP64)
-        go(launch_tiles<M, double, M::NSHELL>);
-      else if (plan.wide)
-        go(launch_tiles<M, float, M::ORDER == 3 ? 2 : 1>);
+        go(launch_tiles<M, double, 2>);
       else
-        go(launch_tiles<M, float, M::NSHELL>);
+        go(launch_tiles<M, float, M::ORDER == 3 ? 2 : 1>);
       return 0;
     });
     hipError_t e = hipGetLastError();

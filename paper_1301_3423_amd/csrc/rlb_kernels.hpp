@@ -213,6 +213,31 @@ struct HalfShifts {
 
 __device__ __forceinline__ double add_partner(double v) { return v + __shfl_xor(v, 32); }
 
+// The moments of a cell from those of one member of every pair, summed with
+// theta of point 2k, on the lane with sign sg and its partner.
+__device__ __forceinline__ Moments both_members(Moments m, double sg) {
+  m.Nx *= sg;
+  m.Ny *= sg;
+  m.Nz *= sg;
+  m.T0x *= sg;
+  m.T0y *= sg;
+  m.T0z *= sg;
+  m.N0 = add_partner(m.N0);
+  m.Nx = add_partner(m.Nx);
+  m.Ny = add_partner(m.Ny);
+  m.Nz = add_partner(m.Nz);
+  m.T00 = add_partner(m.T00);
+  m.T0x = add_partner(m.T0x);
+  m.T0y = add_partner(m.T0y);
+  m.T0z = add_partner(m.T0z);
+  m.Txx = add_partner(m.Txx);
+  m.Tyy = add_partner(m.Tyy);
+  m.Tzz = add_partner(m.Tzz);
+  m.Txy = add_partner(m.Txy);
+  m.Txz = add_partner(m.Txz);
+  m.Tyz = add_partner(m.Tyz);
+  return m;
+}
 
 // Float64 populations of the last stash_n pairs of the third-order model
 // wait in LDS between the moment sums and the relaxation (256 B per thread:
@@ -291,26 +316,7 @@ __device__ __forceinline__ void pair_cell_step(InPtr<S, AC> cur, OutPtr<S, AC> n
     asm volatile("" ::: "memory");
   }
   const double sg = static_cast<double>(sigma);
-  mo.Nx *= sg;
-  mo.Ny *= sg;
-  mo.Nz *= sg;
-  mo.T0x *= sg;
-  mo.T0y *= sg;
-  mo.T0z *= sg;
-  mo.N0 = add_partner(mo.N0);
-  mo.Nx = add_partner(mo.Nx);
-  mo.Ny = add_partner(mo.Ny);
-  mo.Nz = add_partner(mo.Nz);
-  mo.T00 = add_partner(mo.T00);
-  mo.T0x = add_partner(mo.T0x);
-  mo.T0y = add_partner(mo.T0y);
-  mo.T0z = add_partner(mo.T0z);
-  mo.Txx = add_partner(mo.Txx);
-  mo.Tyy = add_partner(mo.Tyy);
-  mo.Tzz = add_partner(mo.Tzz);
-  mo.Txy = add_partner(mo.Txy);
-  mo.Txz = add_partner(mo.Txz);
-  mo.Tyz = add_partner(mo.Tyz);
+  mo = both_members(mo, sg);
   Frame fr;
   const unsigned fl = landau_frame(mo, fr);
   const double tau = relaxation_time<M>(rx, fr.n, fr.T);
