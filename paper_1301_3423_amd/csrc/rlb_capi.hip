@@ -162,16 +162,27 @@ bool any_kernel_fits(int64_t cells) {
   return cells >= (M::ORDER == 3 ? 196608 : 98304) && rlb::tile_bytes32_fit<M, float>(cells);
 }
 
-// float64 boxes of at most this many cells are stepped by k_step_split, the
-// rest by the two-lane kernel, whose bits are the same (us per step, two-lane / split,
-// two buffers and in place; third order: 16^3 11.6 / 9.0 and 13.9 / 9.7, 32^3 18.6 /
-// 15.6 and 17.2 / 16.9; second order: 16^3 7.1 / 6.2 and 7.4 / 6.0).  The server's
-// boxes keep the two-lane kernel: it needs half as many workgroups, which counts
-// where other streams keep the chip full (200 steps of 32^3 beside a 256^3 box:
-// 10.5 ms, split 11.5).
+// Whether a float64 box is stepped by k_step_split rather than by the two-lane
+// kernel, whose bits are the same.  The lines lie where the CUs get a second
+// workgroup: the split kernel's hold 32 cells (8192 with one for each of 256 CUs),
+// the two-lane kernel's 64 (16,384) or, in place, 128.  us per step, two-lane / split,
+// rows that are no whole lines unless noted:
+//   third order, two buffers: 12^3 11.0 / 8.5, 17^3 11.6 / 10.3, 20^3 11.3 / 11.7,
+//     13x709x1 11.6 / 12.5, 22^3 12.2 / 12.7, 25^3 13.2 / 12.8, 28^3 19.1 / 14.2, 32^3 (lines) 18.6 /
+//     15.6, 7x67x69 19.9 / 17.0, 33^3 23.9 / 24.5
+//   in place: 12^3 13.1 / 9.1, 20x21x21 16.1 / 15.2, 13x709x1 14.4 / 14.2, 25^3 16.0 / 17.4,
+//     33^3 24.0 / 26.7
+//   second order, two buffers and in place: 13^3 6.9 / 6.1 and 7.1 / 6.0, 7x33x35 7.8 / 7.2
+//     and 7.5 / 7.4, 21x23x22 7.9 / 8.1 and 8.6 / 9.0
+// The server's boxes keep the two-lane kernel: it needs half as many workgroups,
+// which counts where other streams keep the chip full (200 steps of 32^3 beside a
+// 256^3 box: 10.5 ms, split 11.5).
 template <class M>
-constexpr int64_t split_kernel_cells = M::ORDER == 3 ? 36864 : 16384;
-static_assert(rlb::tile_bytes32_fit<rlb::M3, double>(split_kernel_cells<rlb::M3>));
+bool split_kernel_fits(int64_t cells, bool in_place) {
+  static_assert(rlb::tile_bytes32_fit<M, double>(32768));
+  if (M::ORDER == 2) return cells <= 8192;
+  return in_place ? cells <= 9216 : cells <= 6144 || (cells > 16384 && cells <= 32768);
+}
 
 // The step kernels of one box, with or without walls, for access AC (with
 // AA the input and output buffer is the same).
@@ -182,7 +193,7 @@ void launch_step_kernels(rlb_solver *s, const rlb::Geom &g, const rlb::Relax &r)
   void *out = AC == rlb::PULL ? s->buf[1 - s->cur] : s->buf[s->cur];
   // the split kernel has one form of the odd AA step
   constexpr int SAC = AC == rlb::AA_ODD_WIDE ? rlb::AA_ODD : AC;
-  if (s->cfg.precision == RLB_FP64 && s->alone && s->cells <= split_kernel_cells<M>) {
+  if (s->cfg.precision == RLB_FP64 && s->alone && split_kernel_fits<M>(s->cells, AC != rlb::PULL)) {
     const dim3 grid(static_cast<unsigned>((s->cells + 31) / 32)), block(128);
     rlb::k_step_split<M, WALLS, SAC><<<grid, block, 0, s->stream>>>(
         static_cast<const double *>(in), static_cast<double *>(out), g, r, s->status, solid);
