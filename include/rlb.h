@@ -254,16 +254,14 @@ int rlb_set_walls(rlb_solver *s, const uint8_t *solid, void *d_buf, size_t bytes
  * 1 x 1 x n lattice on which only the z displacement of each point moves
  * anything.  A batch holds many tubes of one precision in one caller-owned
  * buffer and advances all of them together: launches of up to five steps
- * (float64: three) spread the cells over the chip, 64 (32) to a workgroup.  Many third-order
- * mixed-precision tubes (some 300 or more; same results) take one persistent
- * launch instead: one workgroup per tube, launched longest-work-first, whose
- * wavefronts take the tube's (step, chunk) work in order and wait only for
- * the neighbouring chunks' previous step.  Every such wait is bounded: after
- * about 0.1 s it gives up and raises RLB_FLAG_STALL in its tube (never
- * expected; the environment variable RLB_TUBE_SPIN_LIMIT, read by
- * rlb_batch_step, lowers the bound to that many polls, for tests of that
- * path, and selects this kernel for any number of such tubes).  Tubes never
- * interact; a failure (status flag) stays in its tube. */
+ * (float64: three) spread the cells over the chip, 64 (32) to a workgroup.
+ * Where the environment variable RLB_TUBE_SPIN_LIMIT is set, rlb_batch_step
+ * sends third-order mixed-precision tubes to the server's kernel instead (same
+ * results; one workgroup per tube, see below), whose wavefronts wait for their
+ * neighbours' work: the variable bounds each wait to that many polls (0: the
+ * default, about 0.1 s), after which RLB_FLAG_STALL is raised in its tube.  It
+ * is there for tests of that path.  Tubes never interact; a failure (status
+ * flag) stays in its tube. */
 typedef struct rlb_tube {
   int32_t n;        /* cells along z, 1 .. 4,194,304 (2^22)                */
   int32_t tau_mode; /* RLB_TAU_FIXED or RLB_TAU_ETA_S                       */
@@ -290,7 +288,9 @@ int rlb_batch_init(rlb_batch *b, int32_t tube, const double *n, const double *ep
 
 /* Tube j advances steps[j] >= 0 steps (0 leaves it untouched), all tubes
  * together.  Every tube with steps[j] > 0 must have been initialised.
- * Asynchronous on the batch's stream. */
+ * Asynchronous on the batch's stream; as with rlb_step, a call whose launches
+ * (up to one per step) exceed what the stream's queue holds, some ten thousand,
+ * returns when the last of them are queued. */
 int rlb_batch_step(rlb_batch *b, const int64_t *steps);
 
 /* Fields of one tube, as rlb_read_fields (U4 holds 4 n values). */

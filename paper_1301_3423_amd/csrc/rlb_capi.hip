@@ -984,14 +984,10 @@ struct TubeJob {
   int64_t steps;
 };
 
-struct TilePlan {
-  int ksteps;
-  double time; // estimate, us
-};
-
 // The steps per launch of least estimated time.
-TilePlan plan_tiles(const std::vector<TubeJob> &jobs, int precision, int order) {
-  TilePlan best{1, -1.0};
+int plan_ksteps(const std::vector<TubeJob> &jobs, int precision, int order) {
+  int best = 1;
+  double least = -1.0;
   const TileCost cost = tile_cost(precision, order);
   for (int k = 1; k <= tile_max_ksteps(precision); ++k) {
     double launches = 0.0, tiles = 0.0;
@@ -1001,23 +997,12 @@ TilePlan plan_tiles(const std::vector<TubeJob> &jobs, int precision, int order) 
       tiles += l * static_cast<double>(tube_tiles(j.d.n, precision, k));
     }
     const double t = cost.launches(k, launches, tiles);
-    if (best.time < 0.0 || t < best.time) best = {k, t};
+    if (least < 0.0 || t < least) {
+      best = k;
+      least = t;
+    }
   }
   return best;
-}
-
-// Whether the one-workgroup-per-tube kernel takes less time.  Batches use it for
-// third-order float32, whose results are the same bits either way: with some
-// 300 tubes or more it keeps every CU at work and computes no cell twice
-// (512 tubes of 200-4000 cells: 217 us per step against 233 by tiles; 96 of
-// them 112 against 50).
-bool flow_is_faster(const std::vector<TubeJob> &jobs, const TilePlan &plan) {
-  double longest = 0.0, all = 0.0;
-  for (const TubeJob &j : jobs) {
-    longest = std::max(longest, (7.0 + j.d.n / 45.0) * static_cast<double>(j.steps));
-    all += static_cast<double>(j.d.n) * static_cast<double>(j.steps) / 5050.0;
-  }
-  return std::max(longest, all) < plan.time;
 }
 
 template <class M, class S, int NG>
@@ -1027,15 +1012,14 @@ void launch_tiles(dim3 grid, void *pops, const rlb::TubeDesc *desc, const int *f
                                                               ksteps, status);
 }
 
-// Advances the jobs by launches of k_tubes_tile, the tubes with the most
-// steps first, so that those which have finished drop off the grid's end.
+// Advances the jobs by launches of k_tubes_tile, k steps each, the tubes with
+// the most steps first, so that those which have finished drop off the grid's end.
 // h_desc, h_first: pinned staging for the jobs' tables, free for the next use
-// once `staged` (if given) has passed; the caller flips each job's current
-// buffer when (steps + ksteps - 1) / ksteps is odd.
-int run_tiles(std::vector<TubeJob> &jobs, const TilePlan &plan, int precision, int order, void *pops,
-              rlb::TubeDesc *h_desc, int *h_first, rlb::TubeDesc *d_desc, int *d_first, unsigned *d_status,
-              hipStream_t st, hipEvent_t staged) {
-  const int k = plan.ksteps;
+// once `staged` has passed; the caller flips each job's current buffer when
+// (steps + k - 1) / k is odd.
+int run_tiles(std::vector<TubeJob> &jobs, int k, int precision, int order, void *pops, rlb::TubeDesc *h_desc,
+              int *h_first, rlb::TubeDesc *d_desc, int *d_first, unsigned *d_status, hipStream_t st,
+              hipEvent_t staged) {
   std::stable_sort(jobs.begin(), jobs.end(), [](const TubeJob &x, const TubeJob &y) { return x.steps > y.steps; });
   const size_t nt = jobs.size();
   int tiles = 0;
@@ -1048,7 +1032,7 @@ int run_tiles(std::vector<TubeJob> &jobs, const TilePlan &plan, int precision, i
   }
   RLB_HIP(hipMemcpyAsync(d_desc, h_desc, nt * sizeof(rlb::TubeDesc), hipMemcpyHostToDevice, st));
   RLB_HIP(hipMemcpyAsync(d_first, h_first, nt * sizeof(int), hipMemcpyHostToDevice, st));
-  if (staged) RLB_HIP(hipEventRecord(staged, st));
+  RLB_HIP(hipEventRecord(staged, st));
   size_t live = nt;
   for (int round = 0;; ++round) {
     while (live > 0 && jobs[live - 1].steps <= static_cast<int64_t>(round) * k) {
@@ -1239,31 +1223,31 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
   }
   if (active == 0) return RLB_OK;
   std::vector<TubeJob> jobs;
-  bool flow = b->precision == RLB_MIXED && b->order == RLB_ORDER3;
-  for (int j = 0; j < b->ntubes; ++j) {
-    if (steps[j] == 0) continue;
-    jobs.push_back({b->desc[j], j, steps[j]});
-    flow = flow && tube_chunks(b->tubes[j].n, b->precision) <= rlb::TUBE_FLOW_CHUNKS<float>;
-  }
-  // tests of the stall path bound the waits of k_tubes to a few polls; where
-  // that is asked for, the batch takes the kernel that waits
+  for (int j = 0; j < b->ntubes; ++j)
+    if (steps[j] > 0) jobs.push_back({b->desc[j], j, steps[j]});
+  // Tiles always, also for many tubes (us per step, third-order mixed, one
+  // workgroup per tube / tiles: 256 tubes of 200 cells 16.1 / 16.4, 400 of 64 18.4 /
+  // 11.2, 300 of 1000 87 / 61, 512 of 200-4000 216 / 185, 256 of 20,000 1016 / 758).
+  // Tests of the server's kernel, whose waits are bounded, reach it from here:
+  // where the variable gives a bound, third-order mixed tubes of any length take it.
+  static_assert(int64_t(rlb::TUBE_FLOW_CHUNKS<float>) * rlb::TUBE_CHUNK<float> >= (1 << 22));
   const char *env = std::getenv("RLB_TUBE_SPIN_LIMIT");
-  const TilePlan plan = plan_tiles(jobs, b->precision, b->order);
-  if (!flow || !(env || flow_is_faster(jobs, plan))) {
+  if (!env || b->precision != RLB_MIXED || b->order != RLB_ORDER3) {
+    const int k = plan_ksteps(jobs, b->precision, b->order);
     int rc = wait_staged(b);
     if (rc != RLB_OK) return rc;
     b->staged_pending = true;
-    rc = run_tiles(jobs, plan, b->precision, b->order, b->pops, b->h_desc, b->h_order, b->d_desc, b->d_order,
+    rc = run_tiles(jobs, k, b->precision, b->order, b->pops, b->h_desc, b->h_order, b->d_desc, b->d_order,
                    b->d_status, b->stream, b->staged);
     if (rc != RLB_OK) return rc;
     for (int j = 0; j < b->ntubes; ++j) {
-      b->desc[j].cur ^= static_cast<int32_t>(((steps[j] + plan.ksteps - 1) / plan.ksteps) & 1);
+      b->desc[j].cur ^= static_cast<int32_t>(((steps[j] + k - 1) / k) & 1);
       b->t[j] += steps[j];
     }
     return RLB_OK;
   }
   std::vector<int64_t> rem(steps, steps + b->ntubes);
-  const int32_t spin_limit = env ? std::max(0, std::atoi(env)) : 0;
+  const int32_t spin_limit = std::max(0, std::atoi(env));
   for (int j = 0; j < b->ntubes; ++j) b->desc[j].spin_limit = spin_limit;
   // one launch per round: each tube takes as many of its remaining steps as
   // keep its (step, chunk) items of the launch below 2^31 (a single round

@@ -449,8 +449,7 @@ inline constexpr int TUBE_BLOCK = 512; // one workgroup fills a CU at two waves 
 // Every dependence of k is on smaller k, all of which were taken earlier,
 // so the work always progresses.  A step count per chunk is kept modulo
 // 256 (chunks in progress are at most a few steps apart).  The server's tubes
-// take this kernel, and large third-order float32 batches; other batches take
-// k_tubes_tile.
+// take this kernel; batches take k_tubes_tile.
 template <class S>
 inline constexpr int TUBE_CHUNK = sizeof(S) == 8 ? 32 : 64;
 // LDS flag bytes: float64 keeps 128 KB for its stash, float32 has no stash
