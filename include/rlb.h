@@ -157,11 +157,13 @@ int rlb_create(rlb_solver **out, const rlb_config *cfg, void *d_buf, size_t byte
 /* Sets every cell to local equilibrium f_i = f_i^eq(n, T, U) with
  * T = eps / (3 n) and U = gamma (1, v) (initial states of Sec. III) and
  * resets t = 0 and the status flags.  n, eps, vx, vy, vz are nx*ny*nz
- * float64 values.  on_device = 0: host arrays, validated on the host
- * (RLB_ENONPHYS if any n <= 0, eps <= 0, |v| >= 1 or a value is not
- * finite; nothing is changed then) and copied through the idle population
- * buffer (AB) or the staging area (AA); the call returns after the copy.  on_device = 1: device arrays,
- * read on the stream; invalid cells raise RLB_FLAG_NONPHYSICAL instead.
+ * float64 values.  on_device = 0: host arrays, validated (RLB_ENONPHYS if any
+ * n <= 0, eps <= 0, |v|^2 = vx*vx + vy*vy + vz*vz >= 1, each operation rounded, or
+ * a value is not finite; state, t and flags are left as they were then) on the
+ * host or, from 65,536 cells on, on the device with the same result, and copied
+ * through the idle population buffer (AB) or the staging area (AA); the call
+ * returns after the copy.  on_device = 1: device arrays, read on the stream;
+ * invalid cells raise RLB_FLAG_NONPHYSICAL instead.
  * The arrays may be released when the call returns (host) or when the
  * stream has passed this point (device). */
 int rlb_init_fields(rlb_solver *s, const double *n, const double *eps, const double *vx,
@@ -282,7 +284,9 @@ int rlb_batch_create(rlb_batch **out, const rlb_tube *tubes, int32_t ntubes, int
                      void *d_buf, size_t bytes, void *stream);
 
 /* Initial fields of one tube (n values each, index = z); semantics and
- * errors as rlb_init_fields.  Resets that tube's t and flags. */
+ * errors as rlb_init_fields (host arrays: checked on the host; the call returns
+ * when they have been copied, the state follows on the stream).  Resets that
+ * tube's t and flags. */
 int rlb_batch_init(rlb_batch *b, int32_t tube, const double *n, const double *eps, const double *vx,
                    const double *vy, const double *vz, int32_t on_device);
 

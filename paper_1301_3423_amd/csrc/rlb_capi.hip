@@ -283,34 +283,36 @@ bool finite_all(const double *a, int64_t n) {
 }
 
 // RLB_OK if every cell of the host fields a[0..5) = n, eps, vx, vy, vz is
-// finite with n > 0, eps > 0 and |v| < 1; else RLB_ENONPHYS and what is wrong.
+// valid; else RLB_ENONPHYS and what is wrong.
 int check_fields(const char *call, const double *const a[5], int64_t C) {
   for (int k = 0; k < 5; ++k)
     if (!finite_all(a[k], C)) return fail(RLB_ENONPHYS, std::string(call) + ": non-finite value");
-  for (int64_t c = 0; c < C; ++c) {
-    const double v2 = a[2][c] * a[2][c] + a[3][c] * a[3][c] + a[4][c] * a[4][c];
-    if (!(a[0][c] > 0.0) || !(a[1][c] > 0.0) || !(v2 < 1.0))
+  for (int64_t c = 0; c < C; ++c)
+    if (!rlb::valid_cell(a[0][c], a[1][c], a[2][c], a[3][c], a[4][c]))
       return fail(RLB_ENONPHYS, std::string(call) + ": cell " + std::to_string(c) + " has n<=0, eps<=0 or |v|>=1");
-  }
   return RLB_OK;
 }
 
 // Copies the fields to dst (C values each) and says whether they pass
-// check_fields, in one sweep (v2 < 1 holds for no NaN or infinity).
+// check_fields, in one sweep.
 bool copy_checked(double *dst, const double *const a[5], int64_t C) {
-  int bad = 0;
+  bool ok = true;
   const double *n = a[0], *e = a[1], *x = a[2], *y = a[3], *z = a[4];
   for (int64_t c = 0; c < C; ++c) {
-    const double v2 = x[c] * x[c] + y[c] * y[c] + z[c] * z[c];
-    bad |= !(n[c] > 0.0) | !(n[c] <= 1.7976931348623157e308) | !(e[c] > 0.0) | !(e[c] <= 1.7976931348623157e308) |
-           !(v2 < 1.0);
+    ok &= rlb::valid_cell(n[c], e[c], x[c], y[c], z[c]);
     dst[c] = n[c];
     dst[C + c] = e[c];
     dst[2 * C + c] = x[c];
     dst[3 * C + c] = y[c];
     dst[4 * C + c] = z[c];
   }
-  return bad == 0;
+  return ok;
+}
+
+// The refusal of fields that copy_checked or k_check found bad.
+int refuse_fields(const char *call, const double *const a[5], int64_t C) {
+  const int rc = check_fields(call, a, C); // says which
+  return rc != RLB_OK ? rc : fail(RLB_ENONPHYS, std::string(call) + ": non-physical value");
 }
 
 // Host fields of this many cells or more are checked on the device, after
@@ -448,10 +450,7 @@ int rlb_init_fields(rlb_solver *s, const double *n, const double *eps, const dou
       rlb::k_check<<<dim3(1024), dim3(rlb::BLOCK), 0, s->stream>>>(stage, C, word);
       RLB_HIP(hipMemcpyAsync(&bad, word, sizeof(unsigned), hipMemcpyDeviceToHost, s->stream));
       RLB_HIP(hipStreamSynchronize(s->stream));
-      if (bad) {
-        const int rc = check_fields("rlb_init_fields", arrs, C); // says which
-        return rc != RLB_OK ? rc : fail(RLB_ENONPHYS, "rlb_init_fields: non-physical value");
-      }
+      if (bad) return refuse_fields("rlb_init_fields", arrs, C);
     }
     dn = stage;
     de = stage + C;
@@ -1172,7 +1171,7 @@ int rlb_batch_init(rlb_batch *b, int32_t tube, const double *n, const double *ep
     const int rc = batch_slot(b, C, &host);
     if (rc != RLB_OK) return rc;
     if (host) {
-      if (!copy_checked(host, arrs, C)) return check_fields("rlb_batch_init", arrs, C);
+      if (!copy_checked(host, arrs, C)) return refuse_fields("rlb_batch_init", arrs, C);
       stage = host; // k_init reads it over the bus
     } else {
       const int bad = check_fields("rlb_batch_init", arrs, C);

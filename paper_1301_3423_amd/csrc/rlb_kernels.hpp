@@ -907,19 +907,25 @@ __global__ void __launch_bounds__(BLOCK) k_init(const double *__restrict__ n_, c
   if (flags) atomicOr(status, flags);
 }
 
+// Whether a cell of host fields is accepted: finite, n > 0, eps > 0 and
+// |v| < 1 (v2 < 1 holds for no NaN or infinity).  On the host and on the device the
+// same bits: the sum is not fused, which would move cells within an ulp of |v| = 1
+// across the line.
+__host__ __device__ inline bool valid_cell(double n, double eps, double vx, double vy, double vz) {
+#pragma clang fp contract(off)
+  constexpr double MAX = 1.7976931348623157e308;
+  const double v2 = vx * vx + vy * vy + vz * vz;
+  return (n > 0.0) & (n <= MAX) & (eps > 0.0) & (eps <= MAX) & (v2 < 1.0);
+}
+
 // Sets *bad if a cell of the fields n, eps, vx, vy, vz (`cells` values each, one
-// after the other) is not finite or has n <= 0, eps <= 0 or |v| >= 1 (v2 < 1
-// holds for no NaN or infinity).
+// after the other) is not valid.
 __global__ void __launch_bounds__(BLOCK) k_check(const double *__restrict__ a, int64_t cells,
                                                  unsigned *__restrict__ bad) {
   bool ok = true;
   for (int64_t c = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; c < cells;
-       c += static_cast<int64_t>(gridDim.x) * BLOCK) {
-    const double n = a[c], eps = a[cells + c];
-    const double vx = a[2 * cells + c], vy = a[3 * cells + c], vz = a[4 * cells + c];
-    const double v2 = vx * vx + vy * vy + vz * vz;
-    ok = ok && n > 0.0 && eps > 0.0 && __builtin_isfinite(n) && __builtin_isfinite(eps) && v2 < 1.0;
-  }
+       c += static_cast<int64_t>(gridDim.x) * BLOCK)
+    ok = ok & valid_cell(a[c], a[cells + c], a[2 * cells + c], a[3 * cells + c], a[4 * cells + c]);
   if (!ok) *bad = 1u;
 }
 
