@@ -1133,9 +1133,13 @@ int rlb_batch_create(rlb_batch **out, const rlb_tube *tubes, int32_t ntubes, int
     if (t.n <= MAX_SLOT_CELLS) b->slot_cells = std::max<int64_t>(b->slot_cells, t.n);
   hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&b->h_desc), ntubes * sizeof(rlb::TubeDesc), hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&b->h_order), ntubes * sizeof(int), hipHostMallocDefault);
-  if (e == hipSuccess && b->slot_cells > 0)
-    e = hipHostMalloc(reinterpret_cast<void **>(&b->h_fields), 7 * b->slot_cells * BATCH_SLOTS * sizeof(double),
-                      hipHostMallocDefault);
+  if (e == hipSuccess && b->slot_cells > 0 &&
+      hipHostMalloc(reinterpret_cast<void **>(&b->h_fields), 7 * b->slot_cells * BATCH_SLOTS * sizeof(double),
+                    hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError(); // without slots fields are staged through the tube's idle buffer
+    b->h_fields = nullptr;
+    b->slot_cells = 0;
+  }
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->staged, hipEventDisableTiming);
   if (e == hipSuccess) {
     e = hipEventCreateWithFlags(&b->slots_read, hipEventDisableTiming);
