@@ -46,8 +46,8 @@ ACCESS = {"pull": 0, "aa_even": 1, "aa_odd": 2}   # the kernels' access template
 
 
 def kernel_name(order, precision, edge, access="pull"):
-    """The step kernel the library launches for a box of this edge (two-buffer
-    pull, or the even or odd step of the in-place AA pattern)."""
+    """The general step kernel of a box of this edge (two-buffer pull, or the even
+    or odd step of the in-place AA pattern); launched_kernel knows the others."""
     a = ACCESS[access]
     two_lane = precision == "fp64" or edge % 64 != 0
     if access == "aa_odd" and two_lane and edge > 6:
@@ -58,6 +58,17 @@ def kernel_name(order, precision, edge, access="pull"):
         return "k_step<Model<%d>, double, false, %d>" % (order, a)
     return ("k_step_row<Model<%d>, float, false, %d>" if edge % 64 == 0
             else "k_step<Model<%d>, float, false, %d>") % (order, a)
+
+
+def launched_kernel(order, precision, edge):
+    """The step kernel the library launches for a two-buffer box of this edge."""
+    cells = edge ** 3
+    if precision == "fp64" and (cells <= (8192 if order == 2 else 6144) or order == 3 and 16384 < cells <= 32768):
+        return "k_step_split<Model<%d>, false, 0>" % order
+    if precision == "mixed" and edge % 64 and cells >= (98304 if order == 2 else 196608):
+        if -(-cells // 64) * 256 * Q_OF_ORDER[order] <= 1 << 32:
+            return "k_step_any<Model<%d>, false>" % order
+    return kernel_name(order, precision, edge)
 
 
 def parse():
@@ -170,6 +181,7 @@ def copy_calibration():
 # --summarize-profiles $OUT` then reads their CSV output and writes one
 # summary per kernel.
 _BOX_FLAGS = "--no-cpu --no-tubes --no-largest --no-configs --serve-requests 0"
+_SMALL_FLAGS = "--no-cpu --no-tubes --no-walls --no-aa --no-largest --no-configs --serve-requests 0"
 _TUBE_FLAGS = "--no-fp64 --no-second-order --no-walls --no-aa --no-configs --serve-requests 0 --no-cpu"
 PROFILE_RUNS = {
     "trace": "rocprofv3 --kernel-trace --stats -f csv -d $OUT/trace -o run -- "
@@ -178,6 +190,18 @@ PROFILE_RUNS = {
                  "python3 $R/bench.py --steps 3 --warmup 1 " + _BOX_FLAGS,
     "pmc_write": "rocprofv3 --pmc WRITE_SIZE -f csv -d $OUT/pmc_write -o run -- "
                  "python3 $R/bench.py --steps 3 --warmup 1 " + _BOX_FLAGS,
+    "trace_101": "rocprofv3 --kernel-trace --stats -f csv -d $OUT/trace_101 -o run -- "
+                 "python3 $R/bench.py --edge 101 --steps 50 --warmup 2 " + _SMALL_FLAGS,
+    "pmc_101_fetch": "rocprofv3 --pmc FETCH_SIZE -f csv -d $OUT/pmc_101_fetch -o run -- "
+                     "python3 $R/bench.py --edge 101 --steps 10 --warmup 1 " + _SMALL_FLAGS,
+    "pmc_101_write": "rocprofv3 --pmc WRITE_SIZE -f csv -d $OUT/pmc_101_write -o run -- "
+                     "python3 $R/bench.py --edge 101 --steps 10 --warmup 1 " + _SMALL_FLAGS,
+    "trace_32": "rocprofv3 --kernel-trace --stats -f csv -d $OUT/trace_32 -o run -- "
+                "python3 $R/bench.py --edge 32 --steps 200 --warmup 2 " + _SMALL_FLAGS,
+    "pmc_32_fetch": "rocprofv3 --pmc FETCH_SIZE -f csv -d $OUT/pmc_32_fetch -o run -- "
+                    "python3 $R/bench.py --edge 32 --steps 50 --warmup 1 " + _SMALL_FLAGS,
+    "pmc_32_write": "rocprofv3 --pmc WRITE_SIZE -f csv -d $OUT/pmc_32_write -o run -- "
+                    "python3 $R/bench.py --edge 32 --steps 50 --warmup 1 " + _SMALL_FLAGS,
     "trace_tubes": "rocprofv3 --kernel-trace --stats -f csv -d $OUT/trace_tubes -o run -- "
                    "python3 $R/bench.py --steps 2 --warmup 1 " + _TUBE_FLAGS,
     "pmc_tubes_fetch": "rocprofv3 --pmc FETCH_SIZE -f csv -d $OUT/pmc_tubes_fetch -o run -- "
@@ -189,12 +213,14 @@ PROFILE_RUNS = {
     "pmc_copy_write": "rocprofv3 --pmc WRITE_SIZE -f csv -d $OUT/pmc_copy_write -o run -- "
                       "python3 $R/bench.py --copy-calibration",
 }
-_BOX_WORKLOAD = "256^3 periodic box, random fields |v|<=0.6 (seed 3), T=1+-10%, eta/s=0.5 (bench.py defaults)"
+TUBE_KERNEL = {"mixed": "k_tubes_tile<Model<3>, float, 2>", "fp64": "k_tubes_tile<Model<3>, double, 2>"}
+_BOX_WORKLOAD = "%d^3 periodic box, random fields |v|<=0.6 (seed 3), T=1+-10%%, eta/s=0.5 (bench.py defaults)"
 
 
 def _profiled_kernels():
     """(file stem, kernel, description, algorithmic bytes per launch, extra
-    workload note) of every step kernel the box legs launch at 256^3."""
+    workload note, edge) of every step kernel the box legs launch at 256^3, and of
+    those that other sizes take."""
     cells = 256 ** 3
     fluid = 256 * (256 - 12) * 256
     out = []
@@ -203,16 +229,25 @@ def _profiled_kernels():
             b = 4 if prec == "mixed" else 8
             what = ("%s-order %s step kernel" % ("third" if order == 3 else "second",
                     "mixed-precision (float32 populations, float64 moments/frame)" if prec == "mixed" else "float64"))
-            out.append((stem + tag, kernel_name(order, prec, 256), what, 2 * Q_OF_ORDER[order] * b * cells, None))
+            out.append((stem + tag, kernel_name(order, prec, 256), what, 2 * Q_OF_ORDER[order] * b * cells, None, 256))
             if order == 3:
                 for acc in ("aa_even", "aa_odd"):
                     out.append((stem + "_" + acc, kernel_name(3, prec, 256, acc),
                                 what + ", %s step of the in-place AA pattern" % acc.split("_")[1],
-                                2 * 128 * b * cells, None))
+                                2 * 128 * b * cells, None, 256))
     out.append(("k_step_row_f32_256cube_walls", "k_step_row<Model<3>, float, true, 0>",
                 "third-order mixed step kernel with solid walls", 2 * 128 * 4 * fluid,
                 "solid slabs of 6 cells at both y ends (4.7% solid); algorithmic bytes counted over the fluid "
-                "cells (solid lanes leave at once)"))
+                "cells (solid lanes leave at once)", 256))
+    for order in (3, 2):
+        nth = "third" if order == 3 else "second"
+        q = Q_OF_ORDER[order]
+        out.append(("k_step_any_f32_101cube" + ("" if order == 3 else "_order2"), launched_kernel(order, "mixed", 101),
+                    nth + "-order mixed-precision step kernel of rows that are no whole number of wavefronts",
+                    2 * q * 4 * 101 ** 3, None, 101))
+    out.append(("k_step_split_f64_32cube", launched_kernel(3, "fp64", 32),
+                "third-order float64 step kernel of small boxes", 2 * 128 * 8 * 32 ** 3,
+                "both population buffers fit the 256 MB last-level cache, so most bytes never reach HBM", 32))
     return out
 
 
@@ -289,22 +324,26 @@ def summarize_profiles(prof_root):
     head = "# commands (run from /tmp with TMPDIR=/tmp; R is the repository root, OUT an output directory):\n"
     tail = "#   then, on any host: python bench.py --summarize-profiles $OUT\n"
     written = []
-    times = _dispatch_times(os.path.join(prof_root, "trace"))
-    fetch = _dispatch_counters(os.path.join(prof_root, "pmc_fetch"), "FETCH_SIZE")
-    write = _dispatch_counters(os.path.join(prof_root, "pmc_write"), "WRITE_SIZE")
-    for stem, kern, what, alg, note in _profiled_kernels():
+    runs = {}
+    for edge, tag in ((256, ""), (101, "_101"), (32, "_32")):
+        runs[edge] = ["trace" + tag, "pmc%s_fetch" % tag, "pmc%s_write" % tag]
+    data = {edge: (_dispatch_times(os.path.join(prof_root, t)),
+                   _dispatch_counters(os.path.join(prof_root, f), "FETCH_SIZE"),
+                   _dispatch_counters(os.path.join(prof_root, w), "WRITE_SIZE")) for edge, (t, f, w) in runs.items()}
+    for stem, kern, what, alg, note, edge in _profiled_kernels():
+        times, fetch, write = data[edge]
         if kern not in times or kern not in fetch or kern not in write:
             continue
         t = times[kern]
         avg = float(np.mean(t))
         fk, wk = float(np.mean(fetch[kern])), float(np.mean(write[kern]))
         rb, wb = fk * 1024 * f_fetch, wk * 1024 * f_write
-        text = ("# rocprofv3 summary: %s %s\n# workload: %s%s\n" % (what, kern, _BOX_WORKLOAD,
+        text = ("# rocprofv3 summary: %s %s\n# workload: %s%s\n" % (what, kern, _BOX_WORKLOAD % edge,
                                                                      "; " + note if note else "")
-                + head + cmds(["trace", "pmc_fetch", "pmc_write", "pmc_copy_fetch", "pmc_copy_write"]) + tail + calib
+                + head + cmds(runs[edge] + ["pmc_copy_fetch", "pmc_copy_write"]) + tail + calib
                 + "# trace: %d dispatches avg %.4f ms (min %.4f, max %.4f)\n" % (len(t), avg, min(t), max(t))
-                + "kernel: %s\nedge: 256\ncells: %d\ndispatches_traced: %d\nkernel_avg_ms: %.4f\n"
-                  % (kern, 256 ** 3, len(t), avg)
+                + "kernel: %s\nedge: %d\ncells: %d\ndispatches_traced: %d\nkernel_avg_ms: %.4f\n"
+                  % (kern, edge, edge ** 3, len(t), avg)
                 + "fetch_size_kib_per_dispatch: %.1f\nwrite_size_kib_per_dispatch: %.1f\n" % (fk, wk)
                 + "read_bytes_per_launch: %d\nwrite_bytes_per_launch: %d\ntraffic_bytes_per_launch: %d\n"
                   % (rb, wb, rb + wb)
@@ -323,28 +362,35 @@ def summarize_profiles(prof_root):
     write = _dispatch_counters(os.path.join(prof_root, "pmc_tubes_write"), "WRITE_SIZE")
     from paper_1301_3423_amd import inputs
     cells = sum(t["N"] for t in inputs.tube_batch(512, 4))
-    # float64 batches run as many launches of k_tubes_tile: no one-launch summary
-    for prec, stem, kern in (("mixed", "k_tubes_f32_512tubes", "k_tubes<Model<3>, float>"),):
+    for prec, stem in (("mixed", "k_tubes_tile_f32_512tubes"), ("fp64", "k_tubes_tile_f64_512tubes")):
+        kern = TUBE_KERNEL[prec]
         if kern not in times or kern not in fetch or kern not in write:
             continue
-        # the bench launches 2 warm-up steps, then the 500 timed ones: the longest dispatch
-        k = int(np.argmax(times[kern]))
-        ms = times[kern][k]
+        # 2 warm-up steps, then the 500 timed ones (their launches are counted), then single tubes
+        t = times[kern]
+        big = next((i for i, x in enumerate(t) if x < 0.25 * max(t)), len(t))
+        t, f, w = t[:big], fetch[kern][:big], write[kern][:big]
+        per = int(round(502.0 / len(t)))
+        skip = -(-2 // per)
+        n = len(t) - skip
+        ms = float(np.sum(t[skip:]))
         b = 4 if prec == "mixed" else 8
         alg = cells * 500 * 2 * 128 * b
-        rb, wb = fetch[kern][k] * 1024 * f_fetch, write[kern][k] * 1024 * f_write
+        rb, wb = float(np.sum(f[skip:])) * 1024 * f_fetch, float(np.sum(w[skip:])) * 1024 * f_write
         text = ("# rocprofv3 summary: third-order tube batch kernel %s\n" % kern
                 + "# workload: 512 shock tubes 1x1xN, N~U{200..4000} (%d cells), T_L/T_R~U(1.1,2), eta/s in "
-                  "{0.01,0.05,0.1,0.2,0.5}, seed 4; one launch of 500 steps\n" % cells
+                  "{0.01,0.05,0.1,0.2,0.5}, seed 4; 500 steps\n" % cells
                 + head + cmds(["trace_tubes", "pmc_tubes_fetch", "pmc_tubes_write", "pmc_copy_fetch",
                                "pmc_copy_write"]) + tail + calib
-                + "# the bench's 2-step warm-up launch is also traced; the figures below are the 500-step launch\n"
-                + "kernel: %s\ntubes: 512\ncells: %d\nsteps_per_launch: 500\nlaunch_ms: %.3f\n" % (kern, cells, ms)
-                + "read_bytes_per_launch: %d\nwrite_bytes_per_launch: %d\ntraffic_bytes_per_launch: %d\n"
-                  % (rb, wb, rb + wb)
-                + "algorithmic_bytes_per_launch: %d\n" % alg
+                + "# algorithmic bytes: one read and one write of every population per step; a launch of several\n"
+                  "# steps reads and writes them once\n"
+                + "kernel: %s\ntubes: 512\ncells: %d\nlaunches: %d\nsteps_per_launch: %d\nkernel_ms_500_steps: %.3f\n"
+                  % (kern, cells, n, per, ms)
+                + "kernel_avg_ms: %.4f\n" % (ms / n)
+                + "read_bytes_500_steps: %d\nwrite_bytes_500_steps: %d\n" % (rb, wb)
+                + "algorithmic_bytes_500_steps: %d\n" % alg
                 + "read_over_algorithmic: %.4f\nwrite_over_algorithmic: %.4f\n" % (2 * rb / alg, 2 * wb / alg)
-                + "achieved_algorithmic_GBps: %.1f\n" % (alg / (ms * 1e-3) / 1e9)
+                + "measured_traffic_GBps: %.1f\n" % ((rb + wb) / (ms * 1e-3) / 1e9)
                 + "source_sha256: %s\n" % digest)
         path = os.path.join(REPO, "profiles", stem + ".txt")
         with open(path, "w") as fh:
@@ -512,7 +558,7 @@ def field_error_summary(a, b):
 
 
 def run_tubes(precision, ntubes=512, steps=500, seed=4):
-    """Many independent shock tubes in one persistent launch."""
+    """Many independent shock tubes in one batch."""
     import torch
     from paper_1301_3423_amd import inputs, rlb
     spec = inputs.tube_batch(ntubes, seed)
@@ -520,7 +566,7 @@ def run_tubes(precision, ntubes=512, steps=500, seed=4):
     b = rlb.Batch(tubes, precision=precision)
     for j, t in enumerate(spec):
         b.init_tube(j, *inputs.shock_tube(t["N"], t["T_left"], t["T_right"]))
-    b.step(2)                       # warm-up launch
+    b.step(2)                       # warm-up
     torch.cuda.synchronize()
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
@@ -652,8 +698,8 @@ def run_riemann():
     """Latency of the 1D Riemann problems: the 1x1x200 tube (T 1.0 | 0.8,
     eta/s 0.1, 200 steps, FP64) and the paper's 1x1x1600 tube (T 1.0 | 0.5,
     eta/s 0.5 and 0.1, t = 3.2 fm/c: 63 steps of the third-order model, 133
-    of the second-order one), each as one persistent launch, wall time from
-    submission of the launch to fields on the host; and the largest
+    of the second-order one), each as one step call, wall time from the call to
+    fields on the host; and the largest
     difference between the two models' velocity profiles."""
     import torch
     from paper_1301_3423_amd import inputs, rlb
@@ -786,7 +832,7 @@ def main():
             r = run_box(edge, prec, fields, args.steps, args.warmup, args.eta_s, order=2)
             print("bench: second-order %s %.1f MLUPS" % (prec, r["mlups"]), file=sys.stderr, flush=True)
             second[prec] = {"value": round(r["mlups"], 2), "unit": "MLUPS", "ms_per_step": round(r["ms_per_step"], 4),
-                            "roofline": roofline(r, kernel_name(2, prec, edge), edge),
+                            "roofline": roofline(r, launched_kernel(2, prec, edge), edge),
                             "status_flags": r["flags"], "conservation_drift": r["conservation_drift"]}
     walls = None
     if not args.no_walls:
@@ -862,9 +908,11 @@ def main():
             r = run_tubes(prec)
             tube_runs[prec] = r
             print("bench: tubes %s %.1f MLUPS" % (prec, r["mlups"]), file=sys.stderr, flush=True)
-            kv = (profile_fields("k_tubes<Model<3>, float>") if prec == "mixed" else None) or {}
-            tubes[prec] = {"value": round(r["mlups"], 2), "unit": "MLUPS", "launch_ms": round(r["ms"], 3),
-                           "achieved_GBps": round(r["achieved_gbs"], 1), "cells": r["cells"],
+            kv = profile_fields(TUBE_KERNEL[prec]) or {}
+            # GB/s of one read and one write of every population per step, which launches of
+            # several steps do not make: the profiled ratios say what they move
+            tubes[prec] = {"value": round(r["mlups"], 2), "unit": "MLUPS", "ms_500_steps": round(r["ms"], 3),
+                           "algorithmic_GBps": round(r["achieved_gbs"], 1), "cells": r["cells"],
                            "tubes_flagged": r["tubes_flagged"],
                            "profiled_read_over_algorithmic": float(kv["read_over_algorithmic"])
                            if "read_over_algorithmic" in kv else None,
@@ -877,7 +925,7 @@ def main():
         print("bench: serving p50 %.3f s p99 %.3f s, %.1f solves/s" % (
             serving["p50_latency_s"], serving["p99_latency_s"], serving["solves_per_s"]), file=sys.stderr, flush=True)
     cpu = None if args.no_cpu else cpu_baseline(args.vmax, args.eta_s)
-    mixed_kernel = kernel_name(3, "mixed", edge)
+    mixed_kernel = launched_kernel(3, "mixed", edge)
     line = {
         "metric": "MLUPS at 256^3 FP64 vs FP32-mixed (% HBM roofline); served p50/p99 latency",
         "value": round(mixed["mlups"], 2),
@@ -906,7 +954,7 @@ def main():
     if fp64 is not None:
         line["fp64"] = {"value": round(fp64["mlups"], 2), "unit": "MLUPS", "dtype": "f64",
                         "ms_per_step": round(fp64["ms_per_step"], 4),
-                        "roofline": roofline(fp64, kernel_name(3, "fp64", edge), edge),
+                        "roofline": roofline(fp64, launched_kernel(3, "fp64", edge), edge),
                         "status_flags": fp64["flags"],
                         "conservation_drift": fp64["conservation_drift"],
                         "mixed_over_fp64": round(mixed["mlups"] / fp64["mlups"], 3)}
@@ -933,7 +981,7 @@ def main():
         line["full_length_runs"] = configs
     if tubes:
         line["tubes"] = {"workload": "512 shock tubes 1x1xN, N~U{200..4000}, T_L/T_R~U(1.1,2), "
-                                     "eta/s in {0.01,0.05,0.1,0.2,0.5}, 500 steps, one persistent launch",
+                                     "eta/s in {0.01,0.05,0.1,0.2,0.5}, 500 steps",
                          **tubes}
         if len(tube_runs) == 2:
             a, b = tube_runs["mixed"], tube_runs["fp64"]

@@ -119,7 +119,7 @@ struct rlb_solver {
   const rlb::Link *d_links = nullptr;
   int64_t nlinks = 0;
   uint64_t solid_hash = 0; // FNV-1a of the mask, 0 without walls
-  bool alone = true;       // false for the server's boxes: other streams keep the chip full
+  bool alone = true;       // false for the server's boxes: other streams keep the chip full (split_kernel_fits)
 };
 
 namespace {
@@ -242,10 +242,11 @@ void launch_step_kernels(rlb_solver *s, const rlb::Geom &g, const rlb::Relax &r)
   }
 }
 
-// float64: the two-lane kernel; float32: one lane per cell when rows are
-// whole wavefronts (nx % 64 == 0), else the two-lane kernel; with walls, the
-// bounce-back copies follow on the same stream.  The AA pattern alternates
-// its even and odd steps in one buffer.
+// float64: the two-lane kernel, or the split one for small boxes
+// (split_kernel_fits); float32: one lane per cell when rows are whole wavefronts
+// (nx % 64 == 0) or the box is large enough (any_kernel_fits, two buffers), else
+// the two-lane kernel; with walls, the bounce-back copies follow on the same
+// stream.  The AA pattern alternates its even and odd steps in one buffer.
 int launch_step(rlb_solver *s) {
   const rlb::Geom g = geom_of(s);
   const rlb::Relax r = relax_of(s);
@@ -1719,9 +1720,11 @@ int64_t tube_round_steps(const rlb_server *sv, const ServeReq *q) {
   return std::min<int64_t>(std::min<int64_t>(q->remaining, cap), std::max<int64_t>(sv->chunk, budget));
 }
 
-// (k_tubes_tile shortens a burst of few requests, 305 to 196 ms for 24, but
-// its launches find no place beside a large box, as k_step_split's; a
-// workgroup that is resident keeps its place.)
+// One workgroup per tube, which keeps its place once it is resident.  (In four
+// wavefronts k_tubes_tile shortened a burst of 24 requests from 305 to 196 ms, but its
+// launches found no place beside a large box: tubes' p99 3.3 s instead of 0.3 on
+// the serving mix.  In two, with the same bits as here, it does find its place
+// beside a batch's or a solver's box; the serving mix has not been run with it.)
 int tubes_advance(rlb_server *sv, int prec, int order, bool &issued) {
   // all resident tubes of this precision and model, one persistent launch
   std::vector<ServeReq *> tubes;

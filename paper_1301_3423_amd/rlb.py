@@ -345,7 +345,7 @@ def batch_bytes(tubes, precision="fp64", order=ORDER3):
 
 class Batch:
     """Many independent 1 x 1 x n shock tubes of one precision and one model,
-    advanced together by one persistent launch per step() call."""
+    advanced together: launches of up to five steps over every tube's cells."""
 
     def __init__(self, tubes, precision="fp64", stream=None, device=None, order=ORDER3):
         import torch
