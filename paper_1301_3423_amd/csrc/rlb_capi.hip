@@ -961,8 +961,8 @@ struct TileCost {
   }
 };
 TileCost tile_cost(int precision, int order) {
-  if (precision == RLB_FP64) return order == RLB_ORDER2 ? TileCost{2.5, 3.0, 1.1, 0.5} : TileCost{3.0, 4.9, 2.2, 1.1};
-  return order == RLB_ORDER2 ? TileCost{2.4, 3.7, 1.4, 0.4} : TileCost{3.1, 4.9, 2.4, 1.0};
+  if (precision == RLB_FP64) return order == RLB_ORDER2 ? TileCost{2.5, 3.0, 1.0, 0.5} : TileCost{3.0, 4.9, 2.2, 0.95};
+  return order == RLB_ORDER2 ? TileCost{2.4, 3.7, 1.0, 0.65} : TileCost{3.1, 4.9, 2.4, 1.0};
 }
 
 int tile_cells(int precision, int k) {
@@ -1006,9 +1006,10 @@ int plan_ksteps(const std::vector<TubeJob> &jobs, int precision, int order) {
 }
 
 template <class M, class S, int NG>
-void launch_tiles(dim3 grid, void *pops, const rlb::TubeDesc *desc, const int *first, int ntubes, int round, int ksteps,
+void launch_tiles(int tiles, void *pops, const rlb::TubeDesc *desc, const int *first, int ntubes, int round, int ksteps,
                   unsigned *status, hipStream_t st) {
-  rlb::k_tubes_tile<M, S, NG><<<grid, dim3(64 * NG), 0, st>>>(static_cast<S *>(pops), desc, first, ntubes, round,
+  const dim3 grid(static_cast<unsigned>((tiles + 7) / 8 * 8)); // for pair_block_order
+  rlb::k_tubes_tile<M, S, NG><<<grid, dim3(64 * NG), 0, st>>>(static_cast<S *>(pops), desc, first, ntubes, tiles, round,
                                                               ksteps, status);
 }
 
@@ -1043,7 +1044,7 @@ int run_tiles(std::vector<TubeJob> &jobs, int k, int precision, int order, void 
     with_model(order, [&](auto m) {
       using M = decltype(m);
       const auto go = [&](auto kernel) {
-        kernel(dim3(tiles), pops, d_desc, d_first, static_cast<int>(live), round, k, d_status, st);
+        kernel(tiles, pops, d_desc, d_first, static_cast<int>(live), round, k, d_status, st);
       };
       if (precision == RLB_FP64)
         go(launch_tiles<M, double, 2>);
@@ -1231,7 +1232,7 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
     if (steps[j] > 0) jobs.push_back({b->desc[j], j, steps[j]});
   // Tiles always, also for many tubes (us per step, third-order mixed, one
   // workgroup per tube / tiles: 256 tubes of 200 cells 16.1 / 16.4, 400 of 64 18.4 /
-  // 11.2, 300 of 1000 87 / 61, 512 of 200-4000 216 / 185, 256 of 20,000 1016 / 758).
+  // 11.2, 300 of 1000 87 / 60, 512 of 200-4000 216 / 171, 256 of 20,000 1016 / 745).
   // Tests of the server's kernel, whose waits are bounded, reach it from here:
   // where the variable gives a bound, third-order mixed tubes of any length take it.
   static_assert(int64_t(rlb::TUBE_FLOW_CHUNKS<float>) * rlb::TUBE_CHUNK<float> >= (1 << 22));

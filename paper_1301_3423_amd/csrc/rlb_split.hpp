@@ -389,13 +389,16 @@ __device__ __forceinline__ int tube_of_tile(const int *__restrict__ first, int n
 // What bounds it.  Few tiles: the chain of one wavefront, 4.9 us per step (third
 // order): the sums over its points, three barriers, the frame, tau or
 // coefficients, its points' equilibrium.  A 200-cell float64 tube takes 5.8 us per
-// step with k = 3 (7.7 with k = 1; as one workgroup per tube, k_tubes, 14.6), one of 1600
-// cells 6.7 (74); mixed, k = 5, 5.5 (9.5) and 5.9 (37).  With more tiles than CUs, the
-// arithmetic: 24 float64 tubes of 200-4000 cells 29 us with k = 2 (196), 512 of
-// them 437 with k = 1 (433, no gain left: 2.5e9 updates/s); mixed 13 (96) and 184
-// (216) with k = 2.  At most 221 registers, none spilled, because the two
-// wavefronts' code is apart from the first load on (one body with branches
-// spilled 136); held to three wavefronts per SIMD it spills 66 and takes half as long again.
+// step with k = 3 (7.8 with k = 1; as one workgroup per tube, k_tubes, 14.6), one of 1600
+// cells 6.1 (74); mixed, k = 5, 5.6 (9.4) and 5.8 (37).  With more tiles than CUs, the
+// arithmetic: 24 float64 tubes of 200-4000 cells 27 us with k = 2 (196), 512 of
+// them 424 with k = 1 (433, little gain: 2.6e9 updates/s); mixed 12.5 (96) and 171
+// (216) with k = 2.  Each XCD takes a contiguous eighth of the tiles, so that the
+// halos of neighbours meet in one L2 (dealt out tile by tile: 512 float64 tubes 437,
+// mixed 184, reading 1.47 and 0.93 of a read per step; 1600 cells 6.7).
+// At most 221 registers, none spilled, because the two wavefronts' code is apart
+// from the first load on (one body with branches spilled 136); held to three
+// wavefronts per SIMD it spills 66 and takes half as long again.
 // NG = 1 (float32): a wavefront holds whole cells and shares nothing; the
 // second-order model's 66 values leave room for that.
 //
@@ -405,7 +408,7 @@ __device__ __forceinline__ int tube_of_tile(const int *__restrict__ first, int n
 template <class M, class S, int NG>
 __global__ void __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2)))
 k_tubes_tile(S *__restrict__ base, const TubeDesc *__restrict__ desc, const int *__restrict__ first, int ntubes,
-             int round, int ksteps, unsigned *__restrict__ status) {
+             int tiles, int round, int ksteps, unsigned *__restrict__ status) {
   using D = Split<M, S, NG>;
   static_assert(D::CELLS == TUBE_TILE<S>);
   constexpr int T = TILE<S>;
@@ -416,7 +419,8 @@ k_tubes_tile(S *__restrict__ base, const TubeDesc *__restrict__ desc, const int 
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const int cell = lane % D::CELLS, m = lane / D::CELLS; // m: which member (float64)
   const int sigma = 1 - 2 * m;
-  const int tile = static_cast<int>(blockIdx.x);
+  const int tile = pair_block_order(blockIdx.x, gridDim.x);
+  if (tile >= tiles) return;
   const int j = tube_of_tile(first, ntubes, tile);
   const TubeDesc d = desc[j];
   const int64_t left = d.steps - static_cast<int64_t>(round) * ksteps;
