@@ -247,7 +247,7 @@ def _profiled_kernels():
                     2 * q * 4 * 101 ** 3, None, 101))
     out.append(("k_step_split_f64_32cube", launched_kernel(3, "fp64", 32),
                 "third-order float64 step kernel of small boxes", 2 * 128 * 8 * 32 ** 3,
-                "both population buffers fit the 256 MB last-level cache, so most bytes never reach HBM", 32))
+                "both population buffers fit the 256 MB last-level cache, which lies behind these counters", 32))
     return out
 
 

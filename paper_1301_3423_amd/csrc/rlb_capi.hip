@@ -1231,8 +1231,8 @@ int rlb_batch_step(rlb_batch *b, const int64_t *steps) {
   for (int j = 0; j < b->ntubes; ++j)
     if (steps[j] > 0) jobs.push_back({b->desc[j], j, steps[j]});
   // Tiles always, also for many tubes (us per step, third-order mixed, one
-  // workgroup per tube / tiles: 256 tubes of 200 cells 16.1 / 16.4, 400 of 64 18.4 /
-  // 11.2, 300 of 1000 87 / 60, 512 of 200-4000 216 / 171, 256 of 20,000 1016 / 745).
+  // workgroup per tube / tiles: 256 tubes of 200 cells 16.2 / 15.3, 400 of 64 18.2 /
+  // 10.7, 300 of 1000 87 / 58, 512 of 200-4000 216 / 171, 256 of 20,000 1015 / 683).
   // Tests of the server's kernel, whose waits are bounded, reach it from here:
   // where the variable gives a bound, third-order mixed tubes of any length take it.
   static_assert(int64_t(rlb::TUBE_FLOW_CHUNKS<float>) * rlb::TUBE_CHUNK<float> >= (1 << 22));
